@@ -115,82 +115,25 @@ __device__ __forceinline__ void decide128(uint32_t key0, uint32_t key1, uint32_t
     for (int w = 0; w < 4; ++w) D[w] = lt[w];
 }
 
-// OR of v over the four lanes of a quad (DPP quad permutations).
-__device__ __forceinline__ uint32_t quad_or(uint32_t v)
+// Transpose of a 4 x 4 word matrix held by the four lanes l, l + 16, l + 32,
+// l + 48 (q = lane / 16), row q in lane q: after it, R[x] of lane q is the old
+// R[q] of lane x.  Each swap exchanges the odd 16-lane rows (permlane16) or the
+// upper half (permlane32) of one register with the even rows or the lower half
+// of another: four instructions, where DPP quad permutations take sixteen.
+__device__ __forceinline__ void rows_transpose(uint32_t (&R)[4])
 {
-    v |= (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, false);   // quad_perm [1, 0, 3, 2]
-    return v | (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, false);   // quad_perm [2, 3, 0, 1]
-}
-
-// Transpose of a 4 x 4 word matrix held by a quad, row q in lane q: after
-// it, R[x] of lane q is the old R[q] of lane x.  Two exchange steps: with
-// lane q ^ 1 the words whose index differs from q in bit 0, then with lane
-// q ^ 2 those that differ in bit 1.
-__device__ __forceinline__ void quad_transpose(uint32_t (&R)[4], uint32_t q)
-{
-    const uint32_t odd1 = (q & 1u) ? ~0u : 0u, odd2 = (q & 2u) ? ~0u : 0u;
-    uint32_t A[4];
 #pragma unroll
-    for (int x = 0; x < 4; ++x) {
-        const uint32_t other = (uint32_t)__builtin_amdgcn_mov_dpp((int)R[x ^ 1], 0xB1, 0xF, 0xF, false);
-        const uint32_t keep = (x & 1) ? odd1 : ~odd1;   // index and lane agree in bit 0
-        A[x] = (keep & R[x]) | (~keep & other);
+    for (int x = 0; x < 2; ++x) {
+        const auto v = __builtin_amdgcn_permlane32_swap(R[x], R[x + 2], false, false);
+        R[x] = v[0];
+        R[x + 2] = v[1];
     }
 #pragma unroll
-    for (int x = 0; x < 4; ++x) {
-        const uint32_t other = (uint32_t)__builtin_amdgcn_mov_dpp((int)A[x ^ 2], 0x4E, 0xF, 0xF, false);
-        const uint32_t keep = (x & 2) ? odd2 : ~odd2;   // ... in bit 1
-        R[x] = (keep & A[x]) | (~keep & other);
+    for (int x = 0; x < 4; x += 2) {
+        const auto v = __builtin_amdgcn_permlane16_swap(R[x], R[x + 1], false, false);
+        R[x] = v[0];
+        R[x + 1] = v[1];
     }
-}
-
-// The same decisions for a group held by the quad of lanes 4i .. 4i+3, lane
-// q holding word q (sites 32q .. 32q+31) and calling this with the other
-// three: in round m lane q draws plane 4m + q, the quad transposes the four
-// draws so that each lane has its own word of the four planes, and each lane
-// runs those planes in order over its 32 sites.  A site's decision is taken at
-// its first plane whose bit differs from its threshold's or after which the
-// threshold has no 1 bit left, as in the plane-by-plane loop; the quad stops
-// when none of its sites is undecided.  D is this lane's word.
-template <int NC>
-__device__ __forceinline__ void decide32_quad(uint32_t key0, uint32_t key1, uint32_t g, uint32_t r, uint32_t t,
-                                              uint32_t c, const uint32_t (&T)[NC], const uint32_t (&cm)[NC][1],
-                                              const uint32_t (&live)[1], uint32_t q, uint32_t (&D)[1])
-{
-    // bit b of NZ[i]: T[i] has a 1 bit below bit b (bits above its lowest 1)
-    uint32_t NZ[NC];
-#pragma unroll
-    for (int i = 0; i < NC; ++i) {
-        const uint32_t low = T[i] & (0u - T[i]);
-        NZ[i] = ~(low | (low - 1u));
-    }
-    uint32_t eq = live[0], lt = 0u;
-    for (uint32_t j0 = 0; j0 < 32u; j0 += 4u) {
-        if (quad_or(eq) == 0u) break;   // the same in the quad's four lanes
-        uint32_t R[4];
-        philox4x32_10(g, r, t, ((j0 + q) << 2) | c, key0, key1, R);
-        quad_transpose(R, q);   // R[x]: this lane's word of plane j0 + x
-        // the round's bits of each class: plane j0 + x compares bit 31 - x
-        uint32_t Tr[NC], Nr[NC];
-#pragma unroll
-        for (int i = 0; i < NC; ++i) {
-            Tr[i] = T[i] << j0;
-            Nr[i] = NZ[i] << j0;
-        }
-#pragma unroll
-        for (int x = 0; x < 4; ++x) {
-            uint32_t tb = 0u, nz = 0u;
-#pragma unroll
-            for (int i = 0; i < NC; ++i) {
-                tb |= cm[i][0] & (uint32_t)((int32_t)(Tr[i] << x) >> 31);
-                nz |= cm[i][0] & (uint32_t)((int32_t)(Nr[i] << x) >> 31);
-            }
-            const uint32_t d = (tb ^ R[x]) | ~nz, l = tb & ~R[x];
-            lt |= eq & l;
-            eq &= ~d;
-        }
-    }
-    D[0] = lt;
 }
 
 // Tile of work-group b of n in an XCD-aware order: work-groups are dispatched

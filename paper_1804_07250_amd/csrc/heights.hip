@@ -23,6 +23,8 @@
 // Context of the weights: sA = #high among NE, SW (corners carrying a) and
 // sB = #high among NW, SE (corners carrying b); W_up/W_down depends on (sA, sB)
 // only.
+#include <type_traits>
+
 #include "../../include/tilings.h"
 #include "height_common.hpp"
 #include "internal.hpp"
@@ -52,11 +54,8 @@ namespace {
 enum { kHeatBath = 0, kMetropolis = 1, kUniform = 2 };
 static_assert(kHeatBath == kModeHeatBath && kMetropolis == kModeMetropolis && kUniform == kModeUniform,
               "kernel modes and TileJob modes agree");
-// Tasks per work-group of a tile, and lanes per work-group of the multi-job
-// kernels (512: room for the step kernels' registers when one-bit and
-// bit-serial jobs share a launch); the tiled kernels take up to 1024 lanes
-// (a quad of lanes per bit-serial task needs at most 69 registers per lane).
-constexpr uint32_t kHeightThreads = 512;
+// (row, group) tasks of a tile (six-vertex: row pairs) and lanes of a work-group.
+constexpr uint32_t kTileTasks = 512;
 constexpr uint32_t kTileThreads = 1024;
 // Layout of a six-vertex threshold table (each layout is its own kernel
 // instantiation, so its registers are allocated for it alone): 9 classes
@@ -134,78 +133,117 @@ __global__ void height_init_kernel(uint32_t *pa, uint32_t *pb, size_t PS, uint32
     if (pb) pb[p * PS + (size_t)y * RS + w] = bits;
 }
 
-// Words of a group that one lane holds: all four when a lane has the task to
-// itself (one-bit decisions), or word q alone when a quad of lanes shares it
-// (lane q of the quad, bit-serial decisions).
-template <uint32_t L>
-constexpr int kWords = L == 4 ? 1 : 4;
-
-template <int W>
-__device__ __forceinline__ void hldw(const uint32_t *p, uint32_t q, uint32_t (&v)[W])
-{
-    if constexpr (W == 4)
-        hld4(p, v);
-    else
-        v[0] = p[q];
-}
-template <int W>
-__device__ __forceinline__ void hldw_plus1(const uint32_t *p, uint32_t q, uint32_t (&v)[W])
-{
-    if constexpr (W == 4)
-        hld4_plus1(p, v);
-    else
-        v[0] = (p[q] >> 1) | (p[q + 1u] << 31);
-}
-template <int W>
-__device__ __forceinline__ void hldw_minus1(const uint32_t *p, uint32_t q, uint32_t (&v)[W])
-{
-    if constexpr (W == 4)
-        hld4_minus1(p, v);
-    else
-        v[0] = (p[q] << 1) | (p[(int)q - 1] >> 31);
-}
-template <int W>
-__device__ __forceinline__ void hstw(uint32_t *p, uint32_t q, const uint32_t (&v)[W])
-{
-    if constexpr (W == 4)
-        hst4(p, v);
-    else
-        p[q] = v[0];
-}
-
-// Bit-serial decisions of one group: plane by plane in one lane (L = 1,
-// kPlanes generator calls per iteration), or by the quad of lanes that holds
-// the group a word per lane (L = 4, this lane is q of the quad).
-template <int NC, uint32_t L, uint32_t kPlanes = 1>
-__device__ __forceinline__ void decide_sites(uint32_t k0, uint32_t k1, uint32_t g, uint32_t r, uint32_t t, uint32_t c,
-                                             const uint32_t (&T)[NC], const uint32_t (&cm)[NC][kWords<L>],
-                                             const uint32_t (&live)[kWords<L>], uint32_t q,
-                                             uint32_t (&D)[kWords<L>])
-{
-    if constexpr (L == 4)
-        decide32_quad<NC>(k0, k1, g, r, t, c, T, cm, live, q, D);
-    else
+// Decisions of the 128 sites of a group held by one lane (the streaming
+// kernels): the one-bit draw, or the bit-serial comparison.
+struct GroupDraws {
+    uint32_t k0, k1, g, r, t, c;
+    uint32_t R0[4];   // plane 0 (one-bit decisions)
+    __device__ __forceinline__ void one_bit(uint32_t (&D)[4]) const
+    {
+#pragma unroll
+        for (int w = 0; w < 4; ++w) D[w] = ~R0[w];
+    }
+    template <int NC, uint32_t kPlanes>
+    __device__ __forceinline__ void compare(const uint32_t (&T)[NC], const uint32_t (&cm)[NC][4],
+                                            const uint32_t (&live)[4], uint32_t (&D)[4]) const
+    {
         decide128<NC, kPlanes>(k0, k1, g, r, t, c, T, cm, live, D);
-}
+    }
+};
+
+// Decisions of one word (32 sites) by lane (row, word) = (lane & 15, lane >> 4)
+// of a wavefront that holds 16 rows of a group.  `A` holds the lane's word of
+// the planes drawn ahead (kAheadPlanes of them; one-bit decisions: plane 0) if
+// `ready`; other planes are drawn four at a time by the four lanes of a row,
+// and handed to their words by a transpose over lanes 16 apart.
+struct WordDraws {
+    uint32_t k0, k1, g, r, t, c, q;
+    bool ready;   // the same in every lane
+    const uint32_t *A;
+    __device__ __forceinline__ void one_bit(uint32_t (&D)[1]) const
+    {
+        if (ready) {
+            D[0] = ~A[0];
+            return;
+        }
+        uint32_t R[4];
+        philox4x32_10(g, r, t, c, k0, k1, R);
+        D[0] = ~(q < 2u ? (q == 0u ? R[0] : R[1]) : (q == 2u ? R[2] : R[3]));
+    }
+    template <int NC, uint32_t kPlanes>
+    __device__ __forceinline__ void compare(const uint32_t (&T)[NC], const uint32_t (&cm)[NC][1],
+                                            const uint32_t (&live)[1], uint32_t (&D)[1]) const
+    {
+        // with several classes, T is kept from being hoisted out of the step
+        // loop: the selectors of every plane and class are more scalars than
+        // there are registers
+        uint32_t Ts[NC];
+        uint32_t half = 0u;   // sites whose threshold is 2^31: plane 0 decides them
+#pragma unroll
+        for (int i = 0; i < NC; ++i) {
+            Ts[i] = T[i];
+            if (NC > 1) {
+                asm volatile("" : "+s"(Ts[i]));
+                half |= cm[i][0] & (Ts[i] == 0x80000000u ? ~0u : 0u);
+            }
+        }
+        // Planes j0 .. j0 + 3, compared from the last to the first: x becomes
+        // "u below T within these planes", e "equal there" (two operations a
+        // plane).  A site that stays equal to the end has u >= T: 0; bits of T
+        // below its lowest 1 change nothing.
+        uint32_t eq = live[0], lt = 0u;
+        auto four = [&](uint32_t j0, uint32_t R0, uint32_t R1, uint32_t R2, uint32_t R3) {
+            const uint32_t R[4] = {R0, R1, R2, R3};
+            uint32_t x = 0u, e = ~0u;
+#pragma unroll
+            for (int y = 3; y >= 0; --y) {
+                uint32_t tb = 0u;
+                if constexpr (NC == 1) {
+                    tb = (uint32_t)((int32_t)(Ts[0] << (j0 + (uint32_t)y)) >> 31);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < NC; ++i)
+                        tb |= cm[i][0] & (uint32_t)((int32_t)(Ts[i] << (j0 + (uint32_t)y)) >> 31);
+                }
+                x = __builtin_amdgcn_bitop3_b32(tb, R[y], x, 0xB2);   // tb ? ~R | x : ~R & x
+                e = __builtin_amdgcn_bitop3_b32(tb, R[y], e, 0x82);   // e & ~(tb ^ R)
+            }
+            lt |= eq & x;
+            eq &= e;
+            if (NC > 1 && j0 == 0u) eq &= ~half;
+        };
+        uint32_t j0 = 0u;
+        if (ready) {
+            static_assert(kAheadPlanes == 8u, "two rounds of planes drawn ahead");
+            four(0u, A[0], A[1], A[2], A[3]);
+            four(4u, A[4], A[5], A[6], A[7]);
+            j0 = kAheadPlanes;
+        }
+        for (; j0 < 32u; j0 += 4u) {
+            if (!__any(eq != 0u)) break;
+            uint32_t R[4];
+            philox4x32_10(g, r, t, ((j0 + q) << 2) | c, k0, k1, R);
+            rows_transpose(R);
+            four(j0, R[0], R[1], R[2], R[3]);
+        }
+        D[0] = lt;
+    }
+};
 
 // Contexts: lozenge heat-bath 1, Metropolis 2 (current up); six-vertex
 // heat-bath 9 classes 3*sA + sB, Metropolis 18 (2*class + current up), or,
 // when a heat-bath table has 5 entries, classes by sA + sB alone.
-template <int MODE, uint32_t L>
-__device__ __forceinline__ void loz_decide(uint32_t k0, uint32_t k1, uint32_t g, uint32_t r, uint32_t t, uint32_t c,
-                                           const Thr &Tall, const uint32_t (&R0)[4],
-                                           const uint32_t (&cur)[kWords<L>], const uint32_t (&live)[kWords<L>],
-                                           uint32_t q, uint32_t (&D)[kWords<L>])
+template <int MODE, int W, class Draws>
+__device__ __forceinline__ void loz_decide(const Draws &dr, const Thr &Tall, const uint32_t (&cur)[W],
+                                           const uint32_t (&live)[W], uint32_t (&D)[W])
 {
-    constexpr int W = kWords<L>;
     if constexpr (MODE == kUniform) {
-#pragma unroll
-        for (int w = 0; w < W; ++w) D[w] = ~R0[w];
+        dr.one_bit(D);
     } else if constexpr (MODE == kHeatBath) {
         uint32_t T[1] = {Tall.v[0]}, cm[1][W];
 #pragma unroll
         for (int w = 0; w < W; ++w) cm[0][w] = ~0u;
-        decide_sites<1, L, 2>(k0, k1, g, r, t, c, T, cm, live, q, D);
+        dr.template compare<1, 2>(T, cm, live, D);
     } else {
         uint32_t T[2] = {Tall.v[0], Tall.v[1]}, cm[2][W];
 #pragma unroll
@@ -213,7 +251,7 @@ __device__ __forceinline__ void loz_decide(uint32_t k0, uint32_t k1, uint32_t g,
             cm[0][w] = ~cur[w];
             cm[1][w] = cur[w];
         }
-        decide_sites<2, L, 2>(k0, k1, g, r, t, c, T, cm, live, q, D);
+        dr.template compare<2, 2>(T, cm, live, D);
     }
 }
 
@@ -221,17 +259,13 @@ __device__ __forceinline__ void loz_decide(uint32_t k0, uint32_t k1, uint32_t g,
 // over the context (first diagonal at m+1) + 2 (second diagonal at m+1)
 // [x2: current state up]; the diagonals (hSW, hSE here) are north SW, SE;
 // south NW, NE; east SW, NW; west SE, NE.
-template <int MODE, uint32_t L>
-__device__ __forceinline__ void sixv_free_decide(uint32_t k0, uint32_t k1, uint32_t g, uint32_t r, uint32_t t,
-                                                 uint32_t c, const Thr &Tall, const uint32_t (&R0)[4],
-                                                 const uint32_t (&hSW)[kWords<L>], const uint32_t (&hSE)[kWords<L>],
-                                                 const uint32_t (&cur)[kWords<L>], const uint32_t (&live)[kWords<L>],
-                                                 uint32_t q, uint32_t (&D)[kWords<L>])
+template <int MODE, int W, class Draws>
+__device__ __forceinline__ void sixv_free_decide(const Draws &dr, const Thr &Tall, const uint32_t (&hSW)[W],
+                                                 const uint32_t (&hSE)[W], const uint32_t (&cur)[W],
+                                                 const uint32_t (&live)[W], uint32_t (&D)[W])
 {
-    constexpr int W = kWords<L>;
     if constexpr (MODE == kUniform) {
-#pragma unroll
-        for (int w = 0; w < W; ++w) D[w] = ~R0[w];
+        dr.one_bit(D);
     } else {
         constexpr int NC = MODE == kMetropolis ? 8 : 4;
         uint32_t T[NC], cm[NC][W];
@@ -249,21 +283,18 @@ __device__ __forceinline__ void sixv_free_decide(uint32_t k0, uint32_t k1, uint3
                     cm[x][w] = m;
                 }
             }
-        decide_sites<NC, L>(k0, k1, g, r, t, c, T, cm, live, q, D);
+        dr.template compare<NC, 1>(T, cm, live, D);
     }
 }
 
-template <int MODE, int KIND, uint32_t L>
-__device__ __forceinline__ void sixv_decide(uint32_t k0, uint32_t k1, uint32_t g, uint32_t r, uint32_t t, uint32_t c,
-                                            const Thr &Tall, const uint32_t (&R0)[4], const uint32_t (&hNE)[kWords<L>],
-                                            const uint32_t (&hNW)[kWords<L>], const uint32_t (&hSW)[kWords<L>],
-                                            const uint32_t (&hSE)[kWords<L>], const uint32_t (&cur)[kWords<L>],
-                                            const uint32_t (&live)[kWords<L>], uint32_t q, uint32_t (&D)[kWords<L>])
+template <int MODE, int KIND, int W, class Draws>
+__device__ __forceinline__ void sixv_decide(const Draws &dr, const Thr &Tall, const uint32_t (&hNE)[W],
+                                            const uint32_t (&hNW)[W], const uint32_t (&hSW)[W],
+                                            const uint32_t (&hSE)[W], const uint32_t (&cur)[W],
+                                            const uint32_t (&live)[W], uint32_t (&D)[W])
 {
-    constexpr int W = kWords<L>;
     if constexpr (MODE == kUniform) {
-#pragma unroll
-        for (int w = 0; w < W; ++w) D[w] = ~R0[w];
+        dr.one_bit(D);
     } else if constexpr (KIND == kKindSum) {
         // thresholds that depend on sA + sB only (a = b): 5 classes s = 0..4
         // (Metropolis: x current state, down then up)
@@ -287,7 +318,7 @@ __device__ __forceinline__ void sixv_decide(uint32_t k0, uint32_t k1, uint32_t g
                 }
             }
         }
-        decide_sites<NC, L>(k0, k1, g, r, t, c, T, cm, live, q, D);
+        dr.template compare<NC, 1>(T, cm, live, D);
     } else {
         constexpr int NC = MODE == kMetropolis ? 18 : 9;
         uint32_t T[NC], cm[NC][W];
@@ -310,178 +341,206 @@ __device__ __forceinline__ void sixv_decide(uint32_t k0, uint32_t k1, uint32_t g
                     }
                 }
         }
-        decide_sites<NC, L>(k0, k1, g, r, t, c, T, cm, live, q, D);
+        dr.template compare<NC, 1>(T, cm, live, D);
     }
 }
 
-// Whether any lane of the quad has a nonzero value (the same answer in the
-// four lanes, so that they call the shared decisions together).
-template <uint32_t L>
-__device__ __forceinline__ uint32_t group_any(uint32_t v)
+// What a colour step needs of W words of lozenge sites: the forward (f) and
+// backward (b) neighbours, the sites that can move and their current state.
+template <int W>
+struct LozWords {
+    uint32_t O[W], f[W], b[W], live[W], cur[W];
+    // m: the words' sites
+    __device__ __forceinline__ bool set(const uint32_t (&f1)[W], const uint32_t (&f2)[W], const uint32_t (&f3)[W],
+                                        const uint32_t (&b1)[W], const uint32_t (&b2)[W], const uint32_t (&b3)[W],
+                                        const uint32_t (&m)[W])
+    {
+        uint32_t any = 0u;
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            f[w] = f1[w];
+            b[w] = b1[w];
+            live[w] = ~(f1[w] ^ f2[w]) & ~(f1[w] ^ f3[w]) & ~(b1[w] ^ b2[w]) & ~(b1[w] ^ b3[w]) & (f1[w] ^ b1[w]) &
+                      m[w];
+            cur[w] = ~(O[w] ^ b1[w]);
+            any |= live[w];
+        }
+        return any != 0u;
+    }
+    template <int MODE, class Draws>
+    __device__ __forceinline__ void move(const Draws &dr, const Thr &Tall)
+    {
+        uint32_t D[W];
+        loz_decide<MODE, W>(dr, Tall, cur, live, D);
+#pragma unroll
+        for (int w = 0; w < W; ++w) O[w] = (O[w] & ~live[w]) | (((D[w] & b[w]) | (~D[w] & f[w])) & live[w]);
+    }
+};
+
+// The same for six-vertex faces: edge neighbours E, Wn, Nn, Sn, diagonal ones,
+// the value `up` of a face at m + 1.  fm: the words' points on the free side.
+template <int W>
+struct SixvWords {
+    uint32_t O[W], E[W], Wn[W], Nn[W], Sn[W], NE[W], NW[W], SE[W], SW[W], fm[W], live[W], up[W], cur[W];
+    __device__ __forceinline__ bool set(bool podd, int side, const uint32_t (&m)[W])
+    {
+        uint32_t any = 0u;
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            const uint32_t eEW = ~(E[w] ^ Wn[w]), eEN = ~(E[w] ^ Nn[w]), eES = ~(E[w] ^ Sn[w]);
+            // free points: the three neighbours off the free side share m
+            const uint32_t lf = side == 1   ? eEW & eES
+                                : side == 2 ? eEW & eEN
+                                : side == 3 ? ~(Wn[w] ^ Nn[w]) & ~(Wn[w] ^ Sn[w])
+                                : side == 4 ? eEN & eES
+                                            : 0u;
+            live[w] = ((eEW & eEN & eES & ~fm[w]) | (lf & fm[w])) & m[w];
+            // residual bit of m + 1 (m read off E, or W across a free east side)
+            const uint32_t ref = side == 3 ? (E[w] & ~fm[w]) | (Wn[w] & fm[w]) : E[w];
+            up[w] = podd ? ref : ~ref;
+            cur[w] = ~(O[w] ^ up[w]);
+            any |= live[w];
+        }
+        return any != 0u;
+    }
+    template <int MODE, int KIND, bool FREE, class Draws>
+    __device__ __forceinline__ void move(const Draws &dr, const Thr &Tall, int side)
+    {
+        uint32_t D[W], hNE[W], hNW[W], hSW[W], hSE[W];
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            hNE[w] = ~(NE[w] ^ up[w]);
+            hNW[w] = ~(NW[w] ^ up[w]);
+            hSW[w] = ~(SW[w] ^ up[w]);
+            hSE[w] = ~(SE[w] ^ up[w]);
+        }
+        if constexpr (FREE) {
+            uint32_t li[W], lf[W], anyf = 0u;
+#pragma unroll
+            for (int w = 0; w < W; ++w) {
+                li[w] = live[w] & ~fm[w];
+                lf[w] = live[w] & fm[w];
+                anyf |= lf[w];
+            }
+            sixv_decide<MODE, KIND, W>(dr, Tall, hNE, hNW, hSW, hSE, cur, li, D);
+            if (__any(anyf != 0u)) {
+                uint32_t Df[W];
+                // context diagonals beside the two cells the flip changes
+                const uint32_t (&c0)[W] = side == 2 ? hNW : side == 4 ? hSE : hSW;
+                const uint32_t (&c1)[W] = side == 1 ? hSE : side == 3 ? hNW : hNE;
+                sixv_free_decide<MODE, W>(dr, Tall, c0, c1, cur, lf, Df);
+#pragma unroll
+                for (int w = 0; w < W; ++w) D[w] = (D[w] & ~fm[w]) | (Df[w] & fm[w]);
+            }
+        } else {
+            sixv_decide<MODE, KIND, W>(dr, Tall, hNE, hNW, hSW, hSE, cur, live, D);
+        }
+#pragma unroll
+        for (int w = 0; w < W; ++w) O[w] = (O[w] & ~live[w]) | (~(D[w] ^ up[w]) & live[w]);
+    }
+};
+
+// Sites of word wi of row y in plane p: lozenge X = 3k + p inside the row's
+// interior, six-vertex faces 1 <= I = 2k + p <= N - 1.
+__device__ __forceinline__ uint32_t loz_row_mask(const Geo &geo, int y, int p, int wi)
 {
-    if constexpr (L == 4) return quad_or(v);
-    return v;
+    const int xlo = imax(0, y - geo.b), xhi = imin(geo.a + geo.c, y + geo.a);
+    return range_mask(wi, floordiv(xlo - p, 3) + 1, floordiv(xhi - p - 1, 3));
+}
+__device__ __forceinline__ uint32_t sixv_row_mask(const Geo &geo, int p, int wi)
+{
+    return range_mask(wi, p == 0 ? 1 : 0, (geo.N - 1 - p) >> 1);
 }
 
-// One lozenge group: sites k = 128 g + (0..127) of plane s0 in row Y.
-// base(p, row) -> pointer to word 4 lg of that plane row (data words, pads
-// around it).  lrow is the row index in the addressed array.
-template <int MODE, bool MASKED, uint32_t L>
-__device__ __forceinline__ void loz_group(uint32_t *base, size_t ps, uint32_t rs, uint32_t lrow, uint32_t lgrp,
-                                          const Geo &geo, int Y, uint32_t g, uint32_t s0, uint32_t colour, uint32_t t,
-                                          const Thr &Tall, uint32_t k0, uint32_t k1, uint32_t q)
+// ---------------------------------------------------------- streaming kernel
+// One lozenge group by one lane: sites k = 128 g + (0..127) of plane s0 in
+// row Y.
+template <int MODE, bool MASKED>
+__device__ __forceinline__ void loz_group(uint32_t *base, size_t ps, uint32_t rs, const Geo &geo, int Y, uint32_t g,
+                                          uint32_t s0, uint32_t colour, uint32_t t, const Thr &Tall, uint32_t k0,
+                                          uint32_t k1)
 {
-    constexpr int W = kWords<L>;
-    uint32_t R0[4] = {0u, 0u, 0u, 0u};
-    if (MODE == kUniform) philox4x32_10(g, (uint32_t)Y, t, colour, k0, k1, R0);
-    auto P = [&](uint32_t p, uint32_t r) { return base + p * ps + (size_t)r * rs + 4u + 4u * lgrp; };
-    uint32_t O[W], f1[W], f2[W], f3[W], b1[W], b2[W], b3[W];
-    hldw<W>(P(s0, lrow), q, O);
-    hldw<W>(P(s0, lrow + 1), q, f2);
-    hldw<W>(P(s0, lrow - 1), q, b2);
+    auto P = [&](uint32_t p, int r) { return base + p * ps + (size_t)r * rs + 4u + 4u * g; };
+    LozWords<4> L;
+    uint32_t f1[4], f2[4], f3[4], b1[4], b2[4], b3[4], m[4];
+    hld4(P(s0, Y), L.O);
+    hld4(P(s0, Y + 1), f2);
+    hld4(P(s0, Y - 1), b2);
     if (s0 < 2) {
-        hldw<W>(P(s0 + 1, lrow), q, f1);
-        hldw<W>(P(s0 + 1, lrow + 1), q, f3);
+        hld4(P(s0 + 1, Y), f1);
+        hld4(P(s0 + 1, Y + 1), f3);
     } else {
-        hldw_plus1<W>(P(0, lrow), q, f1);
-        hldw_plus1<W>(P(0, lrow + 1), q, f3);
+        hld4_plus1(P(0, Y), f1);
+        hld4_plus1(P(0, Y + 1), f3);
     }
     if (s0 > 0) {
-        hldw<W>(P(s0 - 1, lrow), q, b1);
-        hldw<W>(P(s0 - 1, lrow - 1), q, b3);
+        hld4(P(s0 - 1, Y), b1);
+        hld4(P(s0 - 1, Y - 1), b3);
     } else {
-        hldw_minus1<W>(P(2, lrow), q, b1);
-        hldw_minus1<W>(P(2, lrow - 1), q, b3);
+        hld4_minus1(P(2, Y), b1);
+        hld4_minus1(P(2, Y - 1), b3);
     }
-    // interior of row Y: X in (max(0, Y-b), min(a+c, Y+a)), X = 3k + s0
-    const int xlo = imax(0, Y - geo.b), xhi = imin(geo.a + geo.c, Y + geo.a);
-    const int klo = floordiv(xlo - (int)s0, 3) + 1, khi = floordiv(xhi - (int)s0 - 1, 3);
-    // a masked domain: only its sites
-    uint32_t sm[W];
 #pragma unroll
-    for (int w = 0; w < W; ++w) sm[w] = ~0u;
-    if constexpr (MASKED) hldw<W>(geo.site + s0 * geo.sPS + (size_t)Y * geo.sRS + 4u + 4u * g, q, sm);
-    uint32_t live[W], cur[W];
-    uint32_t any = 0u;
+    for (int w = 0; w < 4; ++w) m[w] = ~0u;
+    if constexpr (MASKED) hld4(geo.site + s0 * geo.sPS + (size_t)Y * geo.sRS + 4u + 4u * g, m);
 #pragma unroll
-    for (int w = 0; w < W; ++w) {
-        const int wi = W == 4 ? w : (int)q;   // the word's index in the group
-        const uint32_t m = range_mask((int)(4 * g) + wi, klo, khi) & sm[w];
-        live[w] = ~(f1[w] ^ f2[w]) & ~(f1[w] ^ f3[w]) & ~(b1[w] ^ b2[w]) & ~(b1[w] ^ b3[w]) & (f1[w] ^ b1[w]) & m;
-        cur[w] = ~(O[w] ^ b1[w]);
-        any |= live[w];
-    }
-    if (!group_any<L>(any)) return;
-    uint32_t D[W];
-    loz_decide<MODE, L>(k0, k1, g, (uint32_t)Y, t, colour, Tall, R0, cur, live, q, D);
-#pragma unroll
-    for (int w = 0; w < W; ++w) {
-        const uint32_t nw = (D[w] & b1[w]) | (~D[w] & f1[w]);
-        O[w] = (O[w] & ~live[w]) | (nw & live[w]);
-    }
-    hstw<W>(P(s0, lrow), q, O);
+    for (int w = 0; w < 4; ++w) m[w] &= loz_row_mask(geo, Y, (int)s0, (int)(4u * g) + w);
+    if (!L.set(f1, f2, f3, b1, b2, b3, m)) return;
+    GroupDraws dr{k0, k1, g, (uint32_t)Y, t, colour, {0u, 0u, 0u, 0u}};
+    if (MODE == kUniform) philox4x32_10(g, (uint32_t)Y, t, colour, k0, k1, dr.R0);
+    L.template move<MODE>(dr, Tall);
+    hst4(P(s0, Y), L.O);
 }
 
-// One six-vertex group: faces I = 2k + p, k = 128 g + (0..127), of row J.
-template <int MODE, int KIND, bool MASKED, uint32_t L>
-__device__ __forceinline__ void sixv_group(uint32_t *base, size_t ps, uint32_t rs, uint32_t lrow, uint32_t lgrp,
-                                           const Geo &geo, int J, uint32_t g, uint32_t p, uint32_t colour, uint32_t t,
-                                           const Thr &Tall, uint32_t k0, uint32_t k1, uint32_t q)
+// One six-vertex group by one lane: faces I = 2k + p, k = 128 g + (0..127), of
+// row J.
+template <int MODE, int KIND, bool MASKED>
+__device__ __forceinline__ void sixv_group(uint32_t *base, size_t ps, uint32_t rs, const Geo &geo, int J, uint32_t g,
+                                           uint32_t p, uint32_t colour, uint32_t t, const Thr &Tall, uint32_t k0,
+                                           uint32_t k1)
 {
-    constexpr int W = kWords<L>;
-    uint32_t R0[4] = {0u, 0u, 0u, 0u};
-    if (MODE == kUniform) philox4x32_10(g, (uint32_t)J, t, colour, k0, k1, R0);
-    auto P = [&](uint32_t pl, uint32_t r) { return base + pl * ps + (size_t)r * rs + 4u + 4u * lgrp; };
-    uint32_t O[W], Nn[W], Sn[W], E[W], Wn[W], NE[W], NW[W], SE[W], SW[W];
-    hldw<W>(P(p, lrow), q, O);
-    hldw<W>(P(p, lrow + 1), q, Nn);
-    hldw<W>(P(p, lrow - 1), q, Sn);
+    auto P = [&](uint32_t pl, int r) { return base + pl * ps + (size_t)r * rs + 4u + 4u * g; };
+    SixvWords<4> S;
+    hld4(P(p, J), S.O);
+    hld4(P(p, J + 1), S.Nn);
+    hld4(P(p, J - 1), S.Sn);
     if (p == 0) {
-        hldw<W>(P(1, lrow), q, E);
-        hldw_minus1<W>(P(1, lrow), q, Wn);
-        hldw<W>(P(1, lrow + 1), q, NE);
-        hldw_minus1<W>(P(1, lrow + 1), q, NW);
-        hldw<W>(P(1, lrow - 1), q, SE);
-        hldw_minus1<W>(P(1, lrow - 1), q, SW);
+        hld4(P(1, J), S.E);
+        hld4_minus1(P(1, J), S.Wn);
+        hld4(P(1, J + 1), S.NE);
+        hld4_minus1(P(1, J + 1), S.NW);
+        hld4(P(1, J - 1), S.SE);
+        hld4_minus1(P(1, J - 1), S.SW);
     } else {
-        hldw_plus1<W>(P(0, lrow), q, E);
-        hldw<W>(P(0, lrow), q, Wn);
-        hldw_plus1<W>(P(0, lrow + 1), q, NE);
-        hldw<W>(P(0, lrow + 1), q, NW);
-        hldw_plus1<W>(P(0, lrow - 1), q, SE);
-        hldw<W>(P(0, lrow - 1), q, SW);
+        hld4_plus1(P(0, J), S.E);
+        hld4(P(0, J), S.Wn);
+        hld4_plus1(P(0, J + 1), S.NE);
+        hld4(P(0, J + 1), S.NW);
+        hld4_plus1(P(0, J - 1), S.SE);
+        hld4(P(0, J - 1), S.SW);
     }
-    // interior faces 1 <= I <= N-1 (and, in a masked domain, its sites)
-    const int klo = p == 0 ? 1 : 0, khi = (geo.N - 1 - (int)p) >> 1;
-    uint32_t sm[W], fm[W];
-#pragma unroll
-    for (int w = 0; w < W; ++w) {
-        sm[w] = ~0u;
-        fm[w] = 0u;
-    }
+    uint32_t m[4];
     int side = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        m[w] = ~0u;
+        S.fm[w] = 0u;
+    }
     if constexpr (MASKED) {
-        hldw<W>(geo.site + p * geo.sPS + (size_t)J * geo.sRS + 4u + 4u * g, q, sm);
+        hld4(geo.site + p * geo.sPS + (size_t)J * geo.sRS + 4u + 4u * g, m);
         // points of the free side ignore their (absent) neighbour across it
         if (geo.freep) {
-            hldw<W>(geo.freep + p * geo.sPS + (size_t)J * geo.sRS + 4u + 4u * g, q, fm);
+            hld4(geo.freep + p * geo.sPS + (size_t)J * geo.sRS + 4u + 4u * g, S.fm);
             side = geo.free_side;
         }
     }
-    const bool podd = ((p + (uint32_t)J) & 1u) != 0u;   // parity of I + J
-    uint32_t live[W], up[W], hNE[W], hNW[W], hSW[W], hSE[W], cur[W];
-    uint32_t any = 0u;
 #pragma unroll
-    for (int w = 0; w < W; ++w) {
-        const int wi = W == 4 ? w : (int)q;   // the word's index in the group
-        const uint32_t m = range_mask((int)(4 * g) + wi, klo, khi) & sm[w];
-        const uint32_t eEW = ~(E[w] ^ Wn[w]), eEN = ~(E[w] ^ Nn[w]), eES = ~(E[w] ^ Sn[w]);
-        // free points: the three neighbours off the free side share m
-        const uint32_t lf = side == 1   ? eEW & eES
-                            : side == 2 ? eEW & eEN
-                            : side == 3 ? ~(Wn[w] ^ Nn[w]) & ~(Wn[w] ^ Sn[w])
-                            : side == 4 ? eEN & eES
-                                        : 0u;
-        live[w] = ((eEW & eEN & eES & ~fm[w]) | (lf & fm[w])) & m;
-        // residual bit of m + 1 (m read off E, or W across a free east side)
-        const uint32_t ref = side == 3 ? (E[w] & ~fm[w]) | (Wn[w] & fm[w]) : E[w];
-        up[w] = podd ? ref : ~ref;
-        hNE[w] = ~(NE[w] ^ up[w]);
-        hNW[w] = ~(NW[w] ^ up[w]);
-        hSW[w] = ~(SW[w] ^ up[w]);
-        hSE[w] = ~(SE[w] ^ up[w]);
-        cur[w] = ~(O[w] ^ up[w]);
-        any |= live[w];
-    }
-    if (!group_any<L>(any)) return;
-    uint32_t D[W];
-    if constexpr (MASKED) {
-        uint32_t li[W], lf[W], anyf = 0u;
-#pragma unroll
-        for (int w = 0; w < W; ++w) {
-            li[w] = live[w] & ~fm[w];
-            lf[w] = live[w] & fm[w];
-            anyf |= lf[w];
-        }
-        sixv_decide<MODE, KIND, L>(k0, k1, g, (uint32_t)J, t, colour, Tall, R0, hNE, hNW, hSW, hSE, cur, li, q, D);
-        if (group_any<L>(anyf)) {
-            uint32_t Df[W];
-            // context diagonals beside the two cells the flip changes
-            const uint32_t (&c0)[W] = side == 2 ? hNW : side == 4 ? hSE : hSW;
-            const uint32_t (&c1)[W] = side == 1 ? hSE : side == 3 ? hNW : hNE;
-            sixv_free_decide<MODE, L>(k0, k1, g, (uint32_t)J, t, colour, Tall, R0, c0, c1, cur, lf, q, Df);
-#pragma unroll
-            for (int w = 0; w < W; ++w) D[w] = (D[w] & ~fm[w]) | (Df[w] & fm[w]);
-        }
-    } else {
-        sixv_decide<MODE, KIND, L>(k0, k1, g, (uint32_t)J, t, colour, Tall, R0, hNE, hNW, hSW, hSE, cur, live, q, D);
-    }
-#pragma unroll
-    for (int w = 0; w < W; ++w) {
-        const uint32_t nw = ~(D[w] ^ up[w]);
-        O[w] = (O[w] & ~live[w]) | (nw & live[w]);
-    }
-    hstw<W>(P(p, lrow), q, O);
+    for (int w = 0; w < 4; ++w) m[w] &= sixv_row_mask(geo, (int)p, (int)(4u * g) + w);
+    if (!S.set(((p + (uint32_t)J) & 1u) != 0u, side, m)) return;
+    GroupDraws dr{k0, k1, g, (uint32_t)J, t, colour, {0u, 0u, 0u, 0u}};
+    if (MODE == kUniform) philox4x32_10(g, (uint32_t)J, t, colour, k0, k1, dr.R0);
+    S.template move<MODE, KIND, MASKED>(dr, Tall, side);
+    hst4(P(p, J), S.O);
 }
 
 // Which plane of row y holds the sites of colour c (-1: none in this row).
@@ -497,22 +556,6 @@ __device__ __forceinline__ bool site_row(const Geo &geo, int y, uint32_t rows)
     return y >= 1 && y <= (int)rows - 2;
 }
 
-// GEOM: the model when known at compile time (kGeomLozenge, kGeomSixv), or
-// kGeomAny to read it from geo.
-enum { kGeomAny = 0, kGeomLozenge = 1, kGeomSixv = 2 };
-template <int MODE, int KIND, bool MASKED, uint32_t L = 1, int GEOM = kGeomAny>
-__device__ __forceinline__ void height_group(uint32_t *base, size_t ps, uint32_t rs, uint32_t lrow, uint32_t lgrp,
-                                             const Geo &geo, int y, uint32_t g, uint32_t colour, uint32_t t,
-                                             const Thr &T, uint32_t k0, uint32_t k1, uint32_t q = 0)
-{
-    const int pl = colour_plane(geo, y, colour);
-    if (pl < 0) return;
-    if (GEOM == kGeomLozenge || (GEOM == kGeomAny && geo.model == TL_LOZENGE))
-        loz_group<MODE, MASKED, L>(base, ps, rs, lrow, lgrp, geo, y, g, (uint32_t)pl, colour, t, T, k0, k1, q);
-    else
-        sixv_group<MODE, KIND, MASKED, L>(base, ps, rs, lrow, lgrp, geo, y, g, (uint32_t)pl, colour, t, T, k0, k1, q);
-}
-
 template <int MODE, int KIND, bool MASKED>
 __global__ void __launch_bounds__(256) height_step_kernel(uint32_t *planes, size_t PS, uint32_t RS, uint32_t ng,
                                                           uint32_t rows, Geo geo, uint32_t colour, uint32_t t, Thr T,
@@ -521,129 +564,433 @@ __global__ void __launch_bounds__(256) height_step_kernel(uint32_t *planes, size
     const uint32_t gid = blockIdx.x * blockDim.x + threadIdx.x;
     const uint32_t g = gid % ng, y = gid / ng;
     if (!site_row(geo, (int)y, rows)) return;
-    height_group<MODE, KIND, MASKED>(planes, PS, RS, y, g, geo, (int)y, g, colour, t, T, k0, k1);
+    const int pl = colour_plane(geo, (int)y, colour);
+    if (pl < 0) return;
+    if (geo.model == TL_LOZENGE)
+        loz_group<MODE, MASKED>(planes, PS, RS, geo, (int)y, g, (uint32_t)pl, colour, t, T, k0, k1);
+    else
+        sixv_group<MODE, KIND, MASKED>(planes, PS, RS, geo, (int)y, g, (uint32_t)pl, colour, t, T, k0, k1);
 }
 
-// One tile of the multi-sweep kernel.  LDS: P planes x LR rows x LRS words,
-// LRS = 4*(LG+2) (the pad groups hold the neighbouring groups, or zero).  Local
-// row lr is global row R0 + lr, local group lg is global group G0 + lg.  With a
-// row halo, the rows still valid before sweep s are [rps*s, LR - rps*s) (rps
-// rows go stale per sweep on each side), and only those are computed.  Under
-// the random colour order (RANDOM) step q of the launch (K per sweep) draws
-// its colour and computes rows [q, LR - q).  Lozenge: every row holds sites
-// of every colour; the block has a thread per (row, group) task (blockDim >=
-// LR * LG) and thread tid handles group tid % LG of row base + tid / LG.
-// Six-vertex: only rows of parity c >> 1 hold sites of colour c, so the
-// threads cover those rows alone (blockDim >= ceil(LR / 2) * LG): thread tid
-// handles group tid % LG of the (tid / LG)-th such row from base.
-template <int MODE, int KIND, bool RANDOM, bool MASKED, int GEOM = kGeomAny>
+// ------------------------------------------------------------ tiled kernels
+// One tile, many sweeps.  A tile's state is small, and few of its sites can
+// move at a time (what moves is a band between the frozen parts of an extremal
+// start, or between the arctic regions).  What bounds a launch is the chain of
+// colour steps, each as long as its slowest wavefront's chain of dependent
+// instructions (4 to 5 clocks each, some 35 for a taken branch, 70 to 130 for
+// an LDS read; a Philox call alone is 260).  So:
+//   * a wavefront holds a granule, 16 task rows of one group of 128 sites, a
+//     lane per (row, word of 32 sites), and runs straight-line code per colour;
+//   * a step looks only at granules that can hold a movable site: those that
+//     had one, or have a neighbour that had one, since their sites of the
+//     step's colour were last looked at (`stamp`, the last step with one);
+//   * a granule that had a movable site lately draws ahead while its LDS reads
+//     are under way, a draw being a function of counters known in advance: the
+//     planes 0..7 of the next step (bit-serial decisions; they settle all but
+//     one site in 256) or plane 0 of the next four steps (one-bit decisions).
+//     Each of a row's four lanes makes one draw in four, and a transpose hands
+//     every lane its word of them.  Other draws are made on the spot.
+// A tile with no movable site at all is written back at once.
+//
+// LDS, in words: a guard row, P planes of the state, P planes of the sites
+// that may move (zero outside the tile's inner rows and groups), the stamps of
+// the granules.  Local row lr is global row R0 + lr, local group lg is global group G0 + lg,
+// in slot lg + 1 of its row (the slots around hold the neighbouring groups, or
+// zero).  Rows have an odd number of slots where LDS allows, so that the 16
+// rows of a granule fall in distinct banks; six-vertex rows are kept even rows
+// first, then odd ones, since a colour step takes rows of one parity.
+//
+// With a row halo, the rows still valid before sweep s are [rps*s, LR - rps*s)
+// (rps rows go stale per sweep on each side), and only those move.  Under the
+// random colour order (RANDOM) step n of the launch (K per sweep) draws its
+// colour and moves rows [n, LR - n).
+constexpr uint32_t kWindow = 8;       // steps after its last movable site that a granule draws ahead
+constexpr uint32_t kColourRing = 128; // random order: colours of the steps around the current one
+
+// Word at byte offset `at` of a tile's LDS.
+__device__ __forceinline__ uint32_t ldw(const uint32_t *lds, uint32_t at)
+{
+    return *reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(lds) + at);
+}
+__device__ __forceinline__ void stw(uint32_t *lds, uint32_t at, uint32_t v)
+{
+    *reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(lds) + at) = v;
+}
+// Sites 32 wi + b, b = 0..31, with klo <= site <= khi, as a mask.
+__device__ __forceinline__ uint32_t clamp_mask(int klo, int khi, int wi)
+{
+    const int a = imin(imax(klo - 32 * wi, 0), 32), b = imin(imax(khi + 1 - 32 * wi, 0), 32);
+    return (uint32_t)(0xFFFFFFFFull << a) & ~(uint32_t)(0xFFFFFFFFull << b);
+}
+
+// GEOM: the model.
+enum { kGeomLozenge = 1, kGeomSixv = 2 };
+template <int MODE, int KIND, bool RANDOM, bool MASKED, int GEOM>
 __device__ __forceinline__ void height_tile(uint32_t *lds, const uint32_t *__restrict__ in,
                                             uint32_t *__restrict__ out, size_t PS, uint32_t RS, uint32_t ng,
-                                            uint32_t rows, uint32_t P, const Geo &geo, uint32_t t0,
-                                            uint32_t nsweeps, uint32_t TR, uint32_t TG, uint32_t HR, uint32_t HG,
-                                            uint32_t tile_r, uint32_t tile_g, const Thr &T, uint32_t k0,
-                                            uint32_t k1)
+                                            uint32_t rows, const Geo &geo, uint32_t t0, uint32_t nsweeps,
+                                            uint32_t TR, uint32_t TG, uint32_t HR, uint32_t HG, uint32_t tile_r,
+                                            uint32_t tile_g, const Thr &T, uint32_t k0, uint32_t k1)
 {
-    const uint32_t LR = TR + 2 * HR, LG = TG + 2 * HG, LRS = 4 * (LG + 2);
-    const uint32_t LPS = LR * LRS;
+    constexpr bool ONEBIT = MODE == kUniform, sixv = GEOM == kGeomSixv;
+    constexpr uint32_t P = sixv ? 2u : 3u, K = sixv ? 4u : 3u, rps = sixv ? 2u : 3u;
+    const uint32_t LR = TR + 2 * HR, LG = TG + 2 * HG;
+    const HeightLds lay = height_lds(sixv, LR, LG);
+    // byte strides
+    const uint32_t LRS = 4u * lay.row_words, LPS = lay.plane_rows * LRS, trows = lay.task_rows;
+    const uint32_t H = lay.plane_rows / 2u * LRS;   // six-vertex: odd rows after even ones
+    const uint32_t NG = lay.granules, RB = lay.row_blocks;
+    const uint32_t state = LRS, site = state + P * LPS;
+    uint32_t *stamp = lds + ((site + P * LPS) >> 2);
+    __shared__ uint32_t s_live;   // the tile has a movable site
+    __shared__ uint32_t s_ring[RANDOM ? kColourRing : 1];
     const int R0 = (int)(tile_r * TR) - (int)HR, G0 = (int)(tile_g * TG) - (int)HG;
-    const uint32_t tid = threadIdx.x, nt = blockDim.x;
+    const uint32_t tid = threadIdx.x, nt = blockDim.x, lane = tid & 63u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6), waves = nt >> 6;
+    const uint32_t row = lane & 15u, q = lane >> 4;
+    auto phys = [&](uint32_t lr) { return sixv ? (lr >> 1) * LRS + (lr & 1u) * H : lr * LRS; };
 
-    // load LR rows x (LG + 2) groups (including the pad groups) per plane
-    const uint32_t items = P * LR * (LG + 2);
-    for (uint32_t i = tid; i < items; i += nt) {
-        const uint32_t lg = i % (LG + 2), lr = (i / (LG + 2)) % LR, p = i / ((LG + 2) * LR);
-        const int gr = R0 + (int)lr, gg = G0 - 1 + (int)lg;   // global group, -1 .. ng = pads
-        uint32_t v[4] = {0u, 0u, 0u, 0u};
+    // (slot, row, plane) of item i = tid, tid + nt, ... of nslots x nrows x P
+    auto each = [&](uint32_t nslots, uint32_t nrows, auto &&f) {
+        uint32_t sl = tid % nslots, lr = tid / nslots, p = 0u;
+        const uint32_t dsl = nt % nslots, dlr = nt / nslots;
+        while (true) {
+            while (lr >= nrows) {
+                lr -= nrows;
+                ++p;
+            }
+            if (p >= P) break;
+            f(sl, lr, p);
+            sl += dsl;
+            lr += dlr;
+            if (sl >= nslots) {
+                sl -= nslots;
+                ++lr;
+            }
+        }
+    };
+    // state, and the sites of the inner rows and groups
+    each(LG + 2u, LR, [&](uint32_t sl, uint32_t lr, uint32_t p) {
+        const int gr = R0 + (int)lr, gg = G0 - 1 + (int)sl;   // global group, -1 .. ng = pads
+        uint32_t v[4] = {0u, 0u, 0u, 0u}, m[4] = {0u, 0u, 0u, 0u};
         if (gr >= 0 && gr < (int)rows && gg >= -1 && gg <= (int)ng)
             hld4(in + p * PS + (size_t)gr * RS + 4 + 4 * gg, v);
-        hst4(lds + p * LPS + lr * LRS + 4 * lg, v);
-    }
+        if (sl >= 1u && sl <= LG && gg >= 0 && gg < (int)ng && lr >= 1u && lr + 1u < LR && site_row(geo, gr, rows)) {
+            int klo, khi;
+            if (sixv) {   // faces 1 <= I = 2k + p <= N - 1
+                klo = p == 0u ? 1 : 0;
+                khi = (geo.N - 1 - (int)p) >> 1;
+            } else {      // vertices X = 3k + p inside the row's interior
+                const int xlo = imax(0, gr - geo.b), xhi = imin(geo.a + geo.c, gr + geo.a);
+                klo = (int)((uint32_t)(xlo + 3 - (int)p) / 3u);
+                khi = (int)((uint32_t)(xhi + 2 - (int)p) / 3u) - 1;
+            }
+#pragma unroll
+            for (int w = 0; w < 4; ++w) m[w] = clamp_mask(klo, khi, 4 * gg + w);
+            if constexpr (MASKED) {
+                uint32_t sm[4];
+                hld4(geo.site + p * geo.sPS + (size_t)gr * geo.sRS + 4 + 4 * gg, sm);
+#pragma unroll
+                for (int w = 0; w < 4; ++w) m[w] &= sm[w];
+            }
+        }
+        const uint32_t at = (p * LPS + phys(lr) + 16u * sl) >> 2;
+        hst4(lds + (state >> 2) + at, v);
+        hst4(lds + (site >> 2) + at, m);
+    });
+    if constexpr (RANDOM)
+        for (uint32_t i = tid; i < kColourRing; i += nt) s_ring[i] = step_colour(K * t0 + i, K, k0, k1);
+    for (uint32_t i = tid; i < NG; i += nt) stamp[i] = 0u;
+    if (tid == 0u) s_live = 0u;
     __syncthreads();
 
-    // Tasks: (row, group), six-vertex (row pair, group).  Bit-serial
-    // decisions give each task a quad of lanes that spreads the planes over
-    // its four lanes (L = 4), one-bit decisions one lane; a work-group with
-    // fewer lanes than the tasks need takes them in turns.
-    constexpr uint32_t L = MODE == kUniform ? 1u : 4u;
-    const uint32_t ql = tid % L, slots = nt / L;
-    const bool sixv = geo.model != TL_LOZENGE;
-    const uint32_t ntasks = (sixv ? (LR + 1u) / 2u : LR) * LG;
-    // (row, group) of this lane's first task, and the step to its next one,
-    // divided once here rather than in every colour step
-    const uint32_t task0 = tid / L, r00 = task0 / LG, lg00 = task0 % LG;
-    const uint32_t step_r = slots / LG, step_g = slots % LG;
-    const uint32_t K_colours = sixv ? 4u : 3u;
-    const uint32_t rps = sixv ? 2u : 3u;
-    for (uint32_t s = 0; s < nsweeps; ++s) {
-        for (uint32_t i = 0; i < K_colours; ++i) {
-            // colour, sweep counter of the draws and valid rows of this step
-            uint32_t c = i, t = t0 + s, base = HR ? rps * s : 0u, end = HR ? LR - rps * s : LR;
-            if constexpr (RANDOM) {
-                const uint32_t step = K_colours * t + i, q = K_colours * s + i;
-                c = step_colour(step, K_colours, k0, k1);
-                t = step;
-                base = HR ? q : 0u;
-                end = HR ? LR - q : LR;
+    auto colour_of = [&](uint32_t n) { return RANDOM ? s_ring[n & (kColourRing - 1u)] : n % K; };
+    // six-vertex: local rows of a step of colour c are 2i + odd_rows(c)
+    auto odd_rows = [&](uint32_t c) { return ((uint32_t)R0 & 1u) ^ (c >> 1); };
+
+    // gi / RB (gi * RB < 2^16)
+    const uint32_t invRB = (0xFFFFu + RB) / RB;
+    auto group_of = [&](uint32_t gi) { return (gi * invRB) >> 16; };
+
+    // A granule's lanes: byte offset of this lane's word (plane 0; six-vertex:
+    // of the even row), its local row (six-vertex: the even one), its group.
+    // Lanes past the last task row read that row and move nothing (their local
+    // row is past every valid one).  Lozenges: the word's offsets in the planes
+    // of the row's sites of colours 0, 1 and 2, and which of them is plane 2;
+    // the forward neighbours in the row lie in the next colour's plane (one
+    // word position on from plane 2 to plane 0), the backward ones in the plane
+    // before (one position back from plane 0 to plane 2).
+    struct Lane {
+        uint32_t at, lr, g, gr, off[3], near;
+        bool last[3];
+    };
+    auto lane_of = [&](uint32_t gi) {
+        const uint32_t lg = group_of(gi), rb = gi - lg * RB, i = 16u * rb + row;
+        Lane l;
+        l.at = state + imin(i, trows - 1u) * LRS + 16u * lg + 16u + 4u * q;
+        l.lr = i < trows ? (sixv ? 2u * i : i) : 1u << 30;
+        l.gr = (uint32_t)(R0 + (int)(sixv ? 2u * i : i));
+        l.g = (uint32_t)(G0 + (int)lg);
+        if constexpr (!sixv) {
+            const uint32_t y3 = (l.gr + 3u * 1024u) % 3u;
+#pragma unroll
+            for (uint32_t c = 0; c < 3u; ++c) {
+                const uint32_t d = c + 3u - y3, s = d >= 3u ? d - 3u : d;
+                l.off[c] = l.at + s * LPS;
+                l.last[c] = s == 2u;
             }
-            uint32_t r0 = r00, lg = lg00;
-            for (uint32_t task = task0; task < ntasks; task += slots) {
-                const int gg = G0 + (int)lg;
-                // six-vertex: the first row >= base of parity c >> 1, then every other row
-                const uint32_t lr = sixv ? base + (((uint32_t)(R0 + (int)base) & 1u) ^ (c >> 1)) + 2u * r0 : base + r0;
-                const int gr = R0 + (int)lr;
-                if (gg >= 0 && gg < (int)ng && lr < end && lr >= 1 && lr + 1 < LR && site_row(geo, gr, rows))
-                    height_group<MODE, KIND, MASKED, L, GEOM>(lds, LPS, LRS, lr, lg, geo, gr, (uint32_t)gg, c, t,
-                                                              T, k0, k1, ql);
-                // one-bit decisions: a lane per task, and every plan gives
-                // the work-group at least as many lanes as tasks
-                if constexpr (L == 1) break;
-                r0 += step_r;
-                lg += step_g;
-                if (lg >= LG) {
-                    lg -= LG;
-                    ++r0;
+        }
+        // granule whose stamp this lane reads: lane d < 9 looks at the
+        // neighbourhood (d / 3 - 1, d % 3 - 1)
+        const int d = (int)(lane < 9u ? lane : 4u), l2 = (int)lg + d / 3 - 1, r2 = (int)rb + d % 3 - 1;
+        l.near = l2 >= 0 && l2 < (int)LG && r2 >= 0 && r2 < (int)RB ? (uint32_t)l2 * RB + (uint32_t)r2 : gi;
+        return l;
+    };
+
+    // A colour step's view of a granule: what its words need, and whether any
+    // of its sites in rows [lo, hi) can move.
+    using Words = std::conditional_t<sixv, SixvWords<1>, LozWords<1>>;
+    struct View {
+        Words w;
+        uint32_t o, any;
+        int side;
+    };
+    auto look = [&](auto ctag, const Lane &l, uint32_t lo, uint32_t hi, auto &&meanwhile) {
+        constexpr uint32_t C = decltype(ctag)::value;
+        View v;
+        v.side = 0;
+        if constexpr (!sixv) {
+            constexpr uint32_t F = (C + 1u) % 3u, B = (C + 2u) % 3u;
+            const uint32_t o = l.off[C], f = l.off[F], b = l.off[B];
+            const uint32_t O = ldw(lds, o), f2 = ldw(lds, o + LRS), b2 = ldw(lds, o - LRS);
+            const uint32_t fa = ldw(lds, f), fa1 = ldw(lds, f + 4u), fc = ldw(lds, f + LRS), fc1 = ldw(lds, f + LRS + 4u);
+            const uint32_t ba1 = ldw(lds, b - 4u), ba = ldw(lds, b), bc1 = ldw(lds, b - LRS - 4u), bc = ldw(lds, b - LRS);
+            const uint32_t sm = ldw(lds, o + P * LPS);
+            meanwhile();
+            const uint32_t m[1] = {l.lr - lo < hi - lo ? sm : 0u};
+            const bool wf = l.last[C], wb = l.last[B];   // the own plane is plane 2, plane 0
+            const uint32_t f1[1] = {wf ? __builtin_amdgcn_alignbit(fa1, fa, 1) : fa};
+            const uint32_t f3[1] = {wf ? __builtin_amdgcn_alignbit(fc1, fc, 1) : fc};
+            const uint32_t b1[1] = {wb ? __builtin_amdgcn_alignbit(ba, ba1, 31) : ba};
+            const uint32_t b3[1] = {wb ? __builtin_amdgcn_alignbit(bc, bc1, 31) : bc};
+            const uint32_t f2a[1] = {f2}, b2a[1] = {b2};
+            v.w.O[0] = O;
+            v.o = o;
+            v.w.set(f1, f2a, f3, b1, b2a, b3, m);
+        } else {
+            constexpr uint32_t p = C & 1u;
+            const uint32_t odd = odd_rows(C);
+            // rows J, J + 1, J - 1 in the split order
+            const uint32_t pl = l.at + p * LPS, xl = l.at + (1u - p) * LPS;
+            const uint32_t a0 = odd ? H : 0u, aN = odd ? LRS : H, aS = odd ? 0u : H - LRS;
+            const uint32_t x = xl + a0, xN = xl + aN, xS = xl + aS;
+            SixvWords<1> &S = v.w;
+            v.o = pl + a0;
+            const uint32_t O = ldw(lds, v.o), Nn = ldw(lds, pl + aN), Sn = ldw(lds, pl + aS);
+            const uint32_t sm = ldw(lds, v.o + P * LPS);
+            // the other plane's words beside: to the left of even, to the right of odd columns
+            const uint32_t x0 = ldw(lds, x), n0 = ldw(lds, xN), s0 = ldw(lds, xS);
+            const uint32_t x1 = ldw(lds, p ? x + 4u : x - 4u), n1 = ldw(lds, p ? xN + 4u : xN - 4u),
+                           s1 = ldw(lds, p ? xS + 4u : xS - 4u);
+            meanwhile();
+            const uint32_t m[1] = {l.lr + odd - lo < hi - lo ? sm : 0u};
+            S.fm[0] = 0u;
+            if constexpr (MASKED) {
+                if (geo.freep) {
+                    v.side = geo.free_side;
+                    // a site lies inside the state, its lane may be a halo row outside
+                    if (m[0]) S.fm[0] = geo.freep[p * geo.sPS + (size_t)(l.gr + odd) * geo.sRS + 4u + 4u * l.g + q];
                 }
             }
-            __syncthreads();
+            S.O[0] = O;
+            S.Nn[0] = Nn;
+            S.Sn[0] = Sn;
+            auto west = [](uint32_t w, uint32_t beside) { return p ? w : __builtin_amdgcn_alignbit(w, beside, 31); };
+            auto east = [](uint32_t w, uint32_t beside) { return p ? __builtin_amdgcn_alignbit(beside, w, 1) : w; };
+            S.E[0] = east(x0, x1);
+            S.Wn[0] = west(x0, x1);
+            S.NE[0] = east(n0, n1);
+            S.NW[0] = west(n0, n1);
+            S.SE[0] = east(s0, s1);
+            S.SW[0] = west(s0, s1);
+            S.set(((p + l.gr + odd) & 1u) != 0u, v.side, m);
+        }
+        v.any = __any(v.w.live[0] != 0u);
+        return v;
+    };
+    auto row_of = [&](const Lane &l, uint32_t c) { return sixv ? l.gr + odd_rows(c) : l.gr; };
+    // The draws of a granule ahead: bit-serial, planes 0..7 for colour c, counter
+    // t; one-bit, plane 0 for the steps n .. n + 3.
+    auto draw = [&](const Lane &l, uint32_t n, uint32_t c, uint32_t t, uint32_t (&A)[ONEBIT ? 4 : kAheadPlanes]) {
+        if constexpr (ONEBIT) {
+            const uint32_t cq = colour_of(n + q), tq = RANDOM ? K * t0 + n + q : t0 + (n + q) / K;
+            philox4x32_10(l.g, row_of(l, cq), tq, cq, k0, k1, A);
+            rows_transpose(A);
+        } else {
+#pragma unroll
+            for (uint32_t h = 0; h < kAheadPlanes / 4u; ++h) {
+                uint32_t R[4];
+                philox4x32_10(l.g, row_of(l, c), t, ((4u * h + q) << 2) | c, k0, k1, R);
+                rows_transpose(R);
+#pragma unroll
+                for (uint32_t x = 0; x < 4u; ++x) A[4u * h + x] = R[x];
+            }
+        }
+    };
+    auto move = [&](auto ctag, const Lane &l, View &v, uint32_t t, bool ready, const uint32_t *A) {
+        constexpr uint32_t C = decltype(ctag)::value;
+        const WordDraws dr{k0, k1, l.g, row_of(l, C), t, C, q, ready, A};
+        if constexpr (sixv)
+            v.w.template move<MODE, KIND, MASKED>(dr, T, v.side);
+        else
+            v.w.template move<MODE>(dr, T);
+        // lanes with nothing to move write to the guard row
+        stw(lds, v.w.live[0] ? v.o : 4u * q, v.w.O[0]);
+    };
+    // f(colour as a compile-time constant)
+    auto with_colour = [&](uint32_t c, auto &&f) {
+        if (c == 0u) f(std::integral_constant<uint32_t, 0u>{});
+        else if (c == 1u) f(std::integral_constant<uint32_t, 1u>{});
+        else if (K == 3u || c == 2u) f(std::integral_constant<uint32_t, 2u>{});
+        else f(std::integral_constant<uint32_t, K - 1u>{});
+    };
+    auto every_colour = [&](auto &&f) {
+        f(std::integral_constant<uint32_t, 0u>{});
+        f(std::integral_constant<uint32_t, 1u>{});
+        f(std::integral_constant<uint32_t, 2u>{});
+        if constexpr (K == 4u) f(std::integral_constant<uint32_t, 3u>{});
+    };
+
+    if (LR >= 3u) {
+        const Lane first = lane_of(wave < NG ? wave : 0u);
+        // granules with a site that can move, in any colour; none: the tile
+        // stays as it is
+        bool live0 = false;   // of this wavefront's first granule
+        for (uint32_t gi = wave; gi < NG; gi += waves) {
+            const Lane l = gi == wave ? first : lane_of(gi);
+            uint32_t any = 0u;
+            every_colour([&](auto ctag) { any |= look(ctag, l, 0u, LR, [] {}).any; });
+            if (any) {
+                stamp[gi] = 1u;
+                s_live = 1u;
+            }
+            if (gi == wave) live0 = any != 0u;
+        }
+        __syncthreads();
+        const uint32_t steps = K * nsweeps;
+        auto can_move = [&](uint32_t near, uint32_t n) {   // since the step's colour was last looked at
+            const uint32_t st = stamp[near];
+            return __any(st != 0u && (RANDOM || st + K >= n)) != 0;
+        };
+        if (s_live != 0u && NG <= waves) {
+            // a granule per wavefront, its draws ahead in registers
+            uint32_t A[ONEBIT ? 4 : kAheadPlanes], N[ONEBIT ? 4 : kAheadPlanes];
+#pragma unroll
+            for (uint32_t x = 0; x < sizeof(A) / 4u; ++x) A[x] = N[x] = 0u;
+            uint32_t seen = live0 && wave < NG ? kWindow : 0u;   // steps left to draw ahead in
+            uint32_t ready = seen;   // A holds the draws (one-bit: of the current four steps)
+            const uint32_t c0 = RANDOM ? (uint32_t)__builtin_amdgcn_readfirstlane(colour_of(0u)) : 0u;
+            if (ready) draw(first, 0u, c0, RANDOM ? K * t0 : t0, A);
+            auto step = [&](auto ctag, uint32_t n, uint32_t t, uint32_t lo, uint32_t cn, uint32_t tn) {
+                if (wave >= NG) return;
+                if (seen == 0u && !can_move(first.near, n)) {
+                    ready = 0u;
+                    return;
+                }
+                const bool ahead = ONEBIT ? seen != 0u && (n & 3u) == 3u : seen != 0u;
+                View v = look(ctag, first, lo, LR - lo, [&] {
+                    if (ahead) draw(first, n + 1u, cn, tn, N);
+                });
+                if (v.any) {
+                    uint32_t a0 = 0u;
+                    if constexpr (ONEBIT) a0 = (n & 2u) ? ((n & 1u) ? A[3] : A[2]) : ((n & 1u) ? A[1] : A[0]);
+                    move(ctag, first, v, t, ready != 0u, ONEBIT ? &a0 : A);
+                    stamp[wave] = n + 1u;
+                    seen = kWindow;
+                } else if (seen) {
+                    --seen;
+                }
+                if (!ONEBIT || (n & 3u) == 3u) {
+                    ready = ahead;
+#pragma unroll
+                    for (uint32_t x = 0; x < sizeof(A) / 4u; ++x) A[x] = N[x];
+                }
+            };
+            if constexpr (RANDOM) {
+                uint32_t c = c0;
+                for (uint32_t n = 0; n < steps; ++n) {
+                    const uint32_t cn = (uint32_t)__builtin_amdgcn_readfirstlane(colour_of(n + 1u));
+                    with_colour(c, [&](auto ctag) { step(ctag, n, K * t0 + n, HR ? n : 0u, cn, K * t0 + n + 1u); });
+                    c = cn;
+                    if (wave == waves - 1u && (n & 63u) == 0u && n)
+                        s_ring[(n + 64u + lane) & (kColourRing - 1u)] = step_colour(K * t0 + n + 64u + lane, K, k0, k1);
+                    __syncthreads();
+                }
+            } else {
+                for (uint32_t s = 0; s < nsweeps; ++s)
+                    every_colour([&](auto ctag) {
+                        constexpr uint32_t C = decltype(ctag)::value;
+                        step(ctag, K * s + C, t0 + s, HR ? rps * s : 0u, C + 1u == K ? 0u : C + 1u,
+                             C + 1u == K ? t0 + s + 1u : t0 + s);
+                        __syncthreads();
+                    });
+            }
+        } else if (s_live != 0u) {
+            // more granules than wavefronts: taken in turns, every draw on the spot
+            for (uint32_t n = 0; n < steps; ++n) {
+                const uint32_t c = RANDOM ? (uint32_t)__builtin_amdgcn_readfirstlane(colour_of(n)) : n % K;
+                const uint32_t t = RANDOM ? K * t0 + n : t0 + n / K, lo = HR ? (RANDOM ? n : rps * (n / K)) : 0u;
+                for (uint32_t gi = wave; gi < NG; gi += waves) {
+                    const Lane l = lane_of(gi);
+                    if (!can_move(l.near, n)) continue;
+                    with_colour(c, [&](auto ctag) {
+                        View v = look(ctag, l, lo, LR - lo, [] {});
+                        if (!v.any) return;
+                        move(ctag, l, v, t, false, nullptr);
+                        stamp[gi] = n + 1u;
+                    });
+                }
+                if constexpr (RANDOM)
+                    if (wave == waves - 1u && (n & 63u) == 0u && n)
+                        s_ring[(n + 64u + lane) & (kColourRing - 1u)] = step_colour(K * t0 + n + 64u + lane, K, k0, k1);
+                __syncthreads();
+            }
         }
     }
 
-    const uint32_t oitems = P * TR * TG;
-    for (uint32_t i = tid; i < oitems; i += nt) {
-        const uint32_t ig = i % TG, ir = (i / TG) % TR, p = i / (TG * TR);
+    each(TG, TR, [&](uint32_t ig, uint32_t ir, uint32_t p) {
         const uint32_t orow = tile_r * TR + ir, og = tile_g * TG + ig;
-        if (orow >= rows || og >= ng) continue;
+        if (orow >= rows || og >= ng) return;
         uint32_t v[4];
-        hld4(lds + p * LPS + (ir + HR) * LRS + 4 * (ig + HG + 1), v);
+        hld4(lds + ((state + p * LPS + phys(ir + HR) + 16u * (ig + HG + 1u)) >> 2), v);
         hst4(out + p * PS + (size_t)orow * RS + 4 + 4 * og, v);
-    }
+    });
 }
 
 // Tiled multi-sweep kernels of one state: one work-group per tile.
 template <int MODE, int KIND, bool RANDOM, bool MASKED>
 __global__ void __launch_bounds__(kTileThreads) height_tiled_kernel(const uint32_t *__restrict__ in,
                                                             uint32_t *__restrict__ out, size_t PS, uint32_t RS,
-                                                            uint32_t ng, uint32_t rows, uint32_t P, Geo geo,
-                                                            uint32_t t0, uint32_t nsweeps, uint32_t TR, uint32_t TG,
+                                                            uint32_t ng, uint32_t rows, Geo geo, uint32_t t0,
+                                                            uint32_t nsweeps, uint32_t TR, uint32_t TG,
                                                             uint32_t HR, uint32_t HG, uint32_t tiles_x, Thr T,
                                                             uint32_t k0, uint32_t k1)
 {
     extern __shared__ uint32_t lds[];
     // plain work-group order: tiles of a hexagon differ in work, and the
     // round-robin dispatch over the XCDs balances them
-    height_tile<MODE, KIND, RANDOM, MASKED, kGeomSixv>(lds, in, out, PS, RS, ng, rows, P, geo, t0, nsweeps, TR, TG,
-                                                       HR, HG, blockIdx.x / tiles_x, blockIdx.x % tiles_x, T, k0, k1);
+    height_tile<MODE, KIND, RANDOM, MASKED, kGeomSixv>(lds, in, out, PS, RS, ng, rows, geo, t0, nsweeps, TR, TG, HR,
+                                                       HG, blockIdx.x / tiles_x, blockIdx.x % tiles_x, T, k0, k1);
 }
 template <int MODE, int KIND, bool RANDOM, bool MASKED>
 __global__ void __launch_bounds__(kTileThreads) loz_tiled_kernel(const uint32_t *__restrict__ in,
                                                         uint32_t *__restrict__ out, size_t PS, uint32_t RS,
-                                                        uint32_t ng, uint32_t rows, uint32_t P, Geo geo, uint32_t t0,
+                                                        uint32_t ng, uint32_t rows, Geo geo, uint32_t t0,
                                                         uint32_t nsweeps, uint32_t TR, uint32_t TG, uint32_t HR,
                                                         uint32_t HG, uint32_t tiles_x, Thr T, uint32_t k0, uint32_t k1)
 {
     extern __shared__ uint32_t lds[];
-    height_tile<MODE, kKindClass, RANDOM, MASKED, kGeomLozenge>(lds, in, out, PS, RS, ng, rows, P, geo, t0, nsweeps,
+    height_tile<MODE, kKindClass, RANDOM, MASKED, kGeomLozenge>(lds, in, out, PS, RS, ng, rows, geo, t0, nsweeps,
                                                                 TR, TG, HR, HG, blockIdx.x / tiles_x,
                                                                 blockIdx.x % tiles_x, T, k0, k1);
 }
@@ -654,14 +1001,20 @@ template <int MODE, int KIND, bool RANDOM, bool MASKED>
 __device__ __forceinline__ void height_item(uint32_t *lds, const TileJob &j, uint32_t tile)
 {
     const Geo geo{j.model, j.a, j.b, j.c, j.N, j.site, j.PS, j.RS, j.freep, j.free_side};
-    height_tile<MODE, KIND, RANDOM, MASKED>(lds, j.in, j.out, j.PS, j.RS, j.ng, j.rows, j.P, geo, j.t0, j.S, j.TR,
-                                            j.TG, j.HR,
-                                    j.HG, tile / j.tiles_x, tile % j.tiles_x, j.T, j.key0, j.key1);
+    const uint32_t tile_r = tile / j.tiles_x, tile_g = tile % j.tiles_x;
+    if (j.model == TL_LOZENGE)   // lozenge tables are always classes
+        height_tile<MODE, kKindClass, RANDOM, MASKED, kGeomLozenge>(lds, j.in, j.out, j.PS, j.RS, j.ng, j.rows, geo,
+                                                                    j.t0, j.S, j.TR, j.TG, j.HR, j.HG, tile_r, tile_g,
+                                                                    j.T, j.key0, j.key1);
+    else
+        height_tile<MODE, KIND, RANDOM, MASKED, kGeomSixv>(lds, j.in, j.out, j.PS, j.RS, j.ng, j.rows, geo, j.t0, j.S,
+                                                           j.TR, j.TG, j.HR, j.HG, tile_r, tile_g, j.T, j.key0,
+                                                           j.key1);
 }
 
 // Every job of a launch has the colour order RANDOM, and site planes iff MASKED.
 template <int MODE, int KIND, bool RANDOM, bool MASKED>
-__global__ void __launch_bounds__(kHeightThreads) height_items_kernel(const TileJob *__restrict__ jobs,
+__global__ void __launch_bounds__(kTileThreads) height_items_kernel(const TileJob *__restrict__ jobs,
                                                                       const TileItem *__restrict__ items)
 {
     extern __shared__ uint32_t lds[];
@@ -682,7 +1035,7 @@ __global__ void __launch_bounds__(kHeightThreads) height_items_kernel(const Tile
 // several rules share one launch instead of a launch per rule on streams
 // joined by events).
 template <bool RANDOM, bool MASKED>
-__global__ void __launch_bounds__(kHeightThreads) height_items_mixed_kernel(const TileJob *__restrict__ jobs,
+__global__ void __launch_bounds__(kTileThreads) height_items_mixed_kernel(const TileJob *__restrict__ jobs,
                                                                             const TileItem *__restrict__ items)
 {
     extern __shared__ uint32_t lds[];
@@ -1023,30 +1376,34 @@ hipError_t height_colour_step(const HeightDev &d, int colour, uint32_t t, const 
                   k0, k1);
 }
 
-HeightTile height_auto_tile(const HeightDev &d, bool uniform, bool metropolis)
+HeightTile height_auto_tile(const HeightDev &d, bool uniform, bool random_order)
 {
     HeightTile t;
-    if (d.rows <= 96 && d.ng <= 4) {   // whole domain in one tile, no halo
+    // Up to 16 granules, a wavefront each: the whole domain in one tile, no halo
+    // and no launch after the first (six-vertex N = 200, one-bit: 0.9 us per
+    // sweep where tiles of 16 rows take 1.5).
+    const HeightLds whole = height_lds(d.model != TL_LOZENGE, d.rows, d.ng);
+    if (whole.granules <= 16u && whole.words) {
         t.TR = d.rows;
         t.TG = d.ng;
-        t.S = 1u << 30;
+        t.S = 1u << 28;
         return t;
     }
-    // Rows up to 8 groups wide are one tile wide (no column halo).  Bit-serial
-    // decisions favour short tiles and few sweeps per launch, one-bit
-    // decisions longer launches; measured on MI355X for the 1024 hexagon
-    // (q = 1999/2000: 5 rows, 3 sweeps) and the N = 1024 squares (heat-bath
-    // 4 rows and 6 sweeps, lazy Metropolis 8 and 8).
+    // Rows up to 8 groups wide are one tile wide (no column halo).  The rows of
+    // a tile with its halo are a whole number of granules (lozenge 16 rows,
+    // six-vertex 32): fewer sweeps per launch pay its fixed time (5 us: reading
+    // the tile, the first look, writing it back) more often, more sweeps grow
+    // the halo.  Measured on MI355X, us per sweep: hexagon 1024, q = 1999/2000,
+    // 8 rows x 4 sweeps 3.6, 14 x 3 4.0, 18 x 5 (2 groups) 4.1; six-vertex N =
+    // 1024 weighted 16 x 12 4.56, 8 x 6 4.66, 32 x 8 4.85; one-bit 16 x 12 1.49,
+    // 8 x 6 1.68, 32 x 16 1.63; random order 16 x 6 2.94, 8 x 3 3.52, 32 x 8 3.04.
     t.TG = d.ng <= 8 ? d.ng : 4;
-    if (uniform) {
-        t.TR = 8;
-        t.S = 16;
-    } else if (d.model == TL_LOZENGE) {
-        t.TR = 5;
-        t.S = 3;
+    if (d.model == TL_LOZENGE) {
+        t.TR = uniform ? 16 : 8;
+        t.S = uniform ? 8 : 4;
     } else {
-        t.TR = metropolis ? 8 : 4;
-        t.S = metropolis ? 8 : 6;
+        t.TR = 16;
+        t.S = random_order ? 6 : 12;
     }
     return t;
 }
@@ -1062,9 +1419,9 @@ bool height_plan(const HeightDev &d, const HeightTile &tile, uint32_t S_max, Til
     const uint32_t TG = tile.TG == 0 ? 1u : (tile.TG < d.ng ? tile.TG : d.ng);
     const uint32_t tiles_x = (d.ng + TG - 1) / TG;
     const uint32_t LG0 = TG + (tiles_x > 1 ? 2u : 0u);
-    // six-vertex tiles run a thread per row pair (one row of each pair is idle
-    // in every colour step), lozenge tiles a thread per row
-    const uint32_t max_rows = (d.model == TL_LOZENGE ? 1u : 2u) * (kHeightThreads / LG0);
+    // six-vertex tasks are row pairs (one row of each pair is idle in every
+    // colour step), lozenge tasks rows
+    const uint32_t max_rows = (d.model == TL_LOZENGE ? 1u : 2u) * (kTileTasks / LG0);
     if (max_rows < 2u * rows_per_sweep + 3u) return false;
     uint32_t TR = tile.TR == 0 ? 1u : (tile.TR < d.rows ? tile.TR : d.rows);
     if (TR < d.rows && TR > max_rows - 2u * rows_per_sweep) TR = max_rows - 2u * rows_per_sweep;
@@ -1074,12 +1431,12 @@ bool height_plan(const HeightDev &d, const HeightTile &tile, uint32_t S_max, Til
     if (tiles_x > 1 && S > 128u / cols_per_sweep) S = 128u / cols_per_sweep;
     if (tiles_y > 1 && S > (max_rows - TR) / (2u * rows_per_sweep)) S = (max_rows - TR) / (2u * rows_per_sweep);
     if (S == 0u) S = 1u;
+    if (S > 1u << 28) S = 1u << 28;   // the kernel counts colour steps in 32 bits
     const uint32_t HR = tiles_y > 1 ? rows_per_sweep * S : 0u;
     const uint32_t HG = tiles_x > 1 ? 1u : 0u;
     const uint32_t LR = TR + 2 * HR, LG = TG + 2 * HG;
-    const uint32_t tasks = height_task_rows(d.model, LR) * LG;
-    const uint32_t lds = d.P * LR * 4u * (LG + 2u) * 4u;
-    if (tasks > kHeightThreads || lds > 160u * 1024u) return false;
+    const HeightLds lay = height_lds(d.model != TL_LOZENGE, LR, LG);
+    if (lay.task_rows * LG > kTileTasks || lay.words == 0u) return false;
     p->S = S;
     p->TR = TR;
     p->TG = TG;
@@ -1087,12 +1444,9 @@ bool height_plan(const HeightDev &d, const HeightTile &tile, uint32_t S_max, Til
     p->HG = HG;
     p->tiles_x = tiles_x;
     p->tiles_y = tiles_y;
-    // a thread per task, a quad per task for bit-serial decisions (the
-    // kernel loops over the tasks when the work-group has fewer lanes)
-    const uint32_t lanes = (tasks * (tile.lanes ? tile.lanes : 1u) + 63) / 64 * 64;
-    const uint32_t cap = tile.items ? kHeightThreads : kTileThreads;
-    p->threads = lanes < cap ? lanes : cap;
-    p->lds = lds;
+    // a wavefront per granule, up to 16
+    p->threads = lay.granules < kTileThreads / 64u ? lay.granules * 64u : kTileThreads;
+    p->lds = lay.words * 4u;
     p->order = tile.order;
     return true;
 }
@@ -1118,7 +1472,7 @@ hipError_t height_tiled_sweeps(HeightDev &d, const HeightTile &tile, uint32_t t0
                      : TL_HEIGHT_PICK_ORDER_MASK(height_tiled_kernel, mode, (int)table_kind(T), p.order, masked);
 #undef TL_LOZ_PICK
         hipError_t e = launch(tm, colours * p.S, k, dim3(p.tiles()), dim3(p.threads), p.lds, s,
-                              (const uint32_t *)d.planes, d.spare, d.PS, d.RS, d.ng, d.rows, d.P, geo_of(d),
+                              (const uint32_t *)d.planes, d.spare, d.PS, d.RS, d.ng, d.rows, geo_of(d),
                               t0 + done, p.S, p.TR, p.TG, p.HR, p.HG, p.tiles_x, T, k0, k1);
         if (e != hipSuccess) return e;
         uint32_t *tmp = d.planes;
@@ -1169,7 +1523,7 @@ hipError_t height_items(const TileJob *jobs, const TileItem *items, uint32_t n_i
                         uint32_t mode, uint32_t kind, uint32_t order, uint32_t masked, hipStream_t s)
 {
     if (n_items == 0) return hipSuccess;
-    if (threads == 0 || threads > kHeightThreads || lds > 160u * 1024u || mode > 2u || kind > 1u)
+    if (threads == 0 || threads > kTileThreads || (threads & 63u) || lds > 160u * 1024u || mode > 2u || kind > 1u)
         return hipErrorInvalidConfiguration;
     auto k = TL_HEIGHT_PICK_ORDER_MASK(height_items_kernel, (int)mode, (int)kind, order, masked);
     hipLaunchKernelGGL(k, dim3(n_items), dim3(threads), lds, s, jobs, items);
@@ -1180,7 +1534,7 @@ hipError_t height_items_mixed(const TileJob *jobs, const TileItem *items, uint32
                               uint32_t lds, uint32_t order, uint32_t masked, hipStream_t s)
 {
     if (n_items == 0) return hipSuccess;
-    if (threads == 0 || threads > kHeightThreads || lds > 160u * 1024u) return hipErrorInvalidConfiguration;
+    if (threads == 0 || threads > kTileThreads || (threads & 63u) || lds > 160u * 1024u) return hipErrorInvalidConfiguration;
     auto k = order ? (masked ? height_items_mixed_kernel<true, true> : height_items_mixed_kernel<true, false>)
                    : (masked ? height_items_mixed_kernel<false, true> : height_items_mixed_kernel<false, false>);
     hipLaunchKernelGGL(k, dim3(n_items), dim3(threads), lds, s, jobs, items);

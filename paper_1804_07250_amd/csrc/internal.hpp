@@ -204,16 +204,43 @@ struct HeightDev {
 struct HeightTile {
     uint32_t TR = 32, TG = 4, S = 8;
     uint32_t order = 0;   // colour order: 0 fixed, 1 random per step
-    uint32_t lanes = 1;   // lanes per task: 1 (one-bit decisions) or 4 (bit-serial, a quad per task)
-    uint32_t items = 0;   // 1: a share of a multi-job launch (work-groups of at most 512 lanes)
 };
+// Task rows of a height tile of LR rows: lozenge one per row, six-vertex
+// one per row pair (each colour step updates rows of one parity only).
+inline __host__ __device__ uint32_t height_task_rows(bool sixv, uint32_t LR) { return sixv ? (LR + 1u) / 2u : LR; }
+// LDS of a height tile (kernel and plan agree on it): words per row and rows
+// per plane, granules (16 task rows x one group), words in all (0: does not
+// fit).
+struct HeightLds {
+    uint32_t row_words, plane_rows, task_rows, row_blocks, granules, words;
+};
+constexpr uint32_t kLdsWords = 160u * 256u - 512u;   // 160 KB, less the kernels' static words
+// Planes a granule with bit-serial decisions draws ahead.
+constexpr uint32_t kAheadPlanes = 8u;
+inline __host__ __device__ HeightLds height_lds(bool sixv, uint32_t LR, uint32_t LG)
+{
+    HeightLds l;
+    l.task_rows = height_task_rows(sixv, LR);
+    l.plane_rows = sixv ? 2u * l.task_rows : LR;
+    l.row_blocks = (l.task_rows + 15u) / 16u;
+    l.granules = l.row_blocks * LG;
+    const uint32_t P = sixv ? 2u : 3u;
+    // an odd number of 4-word slots per row where that fits
+    for (uint32_t slots = (LG + 2u) | 1u;; slots = LG + 2u) {
+        l.row_words = 4u * slots;
+        l.words = l.row_words * (1u + 2u * P * l.plane_rows) + l.granules;
+        if (l.words <= kLdsWords || slots == LG + 2u) break;
+    }
+    if (l.words > kLdsWords) l.words = 0u;
+    return l;
+}
 size_t height_words(HeightDev &d);
 hipError_t height_init(const HeightDev &d, int init_max, hipStream_t s);
 hipError_t height_colour_step(const HeightDev &d, int colour, uint32_t t, const Thr &T, int metropolis,
                               uint64_t seed, hipStream_t s, Timing *tm = nullptr);
 hipError_t height_tiled_sweeps(HeightDev &d, const HeightTile &tile, uint32_t t0, uint32_t n, const Thr &T,
                                int metropolis, uint64_t seed, hipStream_t s, Timing *tm = nullptr);
-HeightTile height_auto_tile(const HeightDev &d, bool uniform, bool metropolis = false);
+HeightTile height_auto_tile(const HeightDev &d, bool uniform, bool random_order);
 // int32 canonical export into dev (rows x (row length) values)
 hipError_t height_export(const HeightDev &d, int32_t *dev, hipStream_t s);
 hipError_t height_observe(const HeightDev &d, uint32_t B, uint32_t bins_x, unsigned long long *bins, hipStream_t s);
@@ -248,9 +275,6 @@ struct TilePlan {
 // Largest launch of at most S_max sweeps the tile shape allows (tile sizes
 // clamped as the single-state launches clamp them); false if none fits.
 bool domino_plan(const DominoDev &d, const DominoTile &tile, uint32_t S_max, TilePlan *p);
-// Thread rows of a height tile of LR rows: lozenge one per row, six-vertex
-// one per row pair (each colour step updates rows of one parity only).
-inline uint32_t height_task_rows(int model, uint32_t LR) { return model == TL_LOZENGE ? LR : (LR + 1u) / 2u; }
 bool height_plan(const HeightDev &d, const HeightTile &tile, uint32_t S_max, TilePlan *p);
 
 // One state's share of a multi-job launch (served form): the state it reads

@@ -463,13 +463,12 @@ public:
         owned_ = false;
         keep_ext_ = false;
     }
-    // Multi-job tiles: a state whose (row, group) tasks fit one work-group (512)
-    // and whose planes fit 64 KB of LDS is one tile (no halo, any sweep
-    // count), unless spread asks for tiles whose tasks, a quad of lanes each
-    // for bit-serial decisions, all run at once (a work-group with fewer lanes
-    // than that takes its tasks in turns).  Larger states are cut into tiles
-    // spanning up to 8 groups, 32, 16 or 8 rows high: the tallest whose tasks
-    // fit 512 lanes, else the one that needs the fewest turns.
+    // Multi-job tiles: a state of at most 512 (row, group) tasks whose planes
+    // fit 64 KB of LDS is one tile (no halo, any sweep count), unless spread
+    // asks for tiles whose granules each have a wavefront.  Larger states are
+    // cut into tiles spanning up to 8 groups, 32, 16 or 8 rows high: the tallest
+    // whose granules each have a wavefront, else the one that needs the fewest
+    // turns.
     bool tile_job(uint32_t t0, uint32_t S_max, const Thr &T, bool metro, uint64_t seed, bool spread, TileJob *j,
                   TilePlan *p) const override
     {
@@ -477,10 +476,10 @@ public:
         HeightTile tile;
         tile.S = S_max;
         tile.order = order;
-        tile.lanes = K.uniform() ? 1u : 4u;
-        tile.items = 1;
-        const uint32_t whole = height_task_rows(d_.model, d_.rows) * d_.ng;
-        if (whole <= 512u && (!spread || whole * tile.lanes <= 512u) &&
+        const bool sixv = !loz();
+        const uint32_t whole = height_task_rows(sixv, d_.rows) * d_.ng;
+        const uint32_t granules = (height_task_rows(sixv, d_.rows) + 15u) / 16u * d_.ng;
+        if (whole <= 512u && (!spread || granules <= 16u) &&
             (size_t)d_.P * d_.rows * 4u * (d_.ng + 2u) * 4u <= 64u * 1024u) {
             tile.TR = d_.rows;
             tile.TG = d_.ng;
@@ -492,8 +491,8 @@ public:
                 tile.TR = TR;
                 TilePlan q;
                 if (!height_plan(d_, tile, S_max, &q)) continue;
-                const uint32_t lanes = height_task_rows(d_.model, q.TR + 2u * q.HR) * (q.TG + 2u * q.HG) * tile.lanes;
-                const uint32_t turns = (lanes + 511u) / 512u;
+                const HeightLds lay = height_lds(sixv, q.TR + 2u * q.HR, q.TG + 2u * q.HG);
+                const uint32_t turns = (lay.granules + 15u) / 16u;
                 if (best_turns == 0 || turns < best_turns) {
                     *p = q;
                     best_turns = turns;
@@ -589,7 +588,7 @@ public:
                 }
             return hipSuccess;
         }
-        HeightTile tile = height_auto_tile(d_, K.uniform(), metro);
+        HeightTile tile = height_auto_tile(d_, K.uniform(), order != 0);
         if (tuned_rows) {
             tile.TR = tuned_rows;
             tile.TG = tuned_groups;
@@ -599,7 +598,6 @@ public:
         if (opt.tile_groups) tile.TG = opt.tile_groups;
         if (opt.sweeps_per_launch) tile.S = opt.sweeps_per_launch;
         tile.order = order;
-        tile.lanes = K.uniform() ? 1u : 4u;
         return height_tiled_sweeps(d_, tile, t0, n, K, metro ? 1 : 0, seed, s, &timing);
     }
     hipError_t observe(uint32_t B, uint32_t bins_x, unsigned long long *bins, hipStream_t s) override
