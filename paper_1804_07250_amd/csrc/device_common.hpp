@@ -144,9 +144,7 @@ __device__ __forceinline__ void rows_transpose(uint32_t (&R)[4])
 __device__ __forceinline__ uint32_t xcd_tile(uint32_t b, uint32_t n)
 {
     const uint32_t x = b & 7u;
-    uint32_t first = 0;
-    for (uint32_t y = 0; y < x; ++y) first += (n + 7u - y) >> 3;
-    return first + (b >> 3);
+    return x * (n >> 3) + (x < (n & 7u) ? x : n & 7u) + (b >> 3);
 }
 
 // Adds the per-cell quantity q of the calling thread to bin (X / B, Y / B).

@@ -25,6 +25,8 @@
 //     recomputed redundantly with the same keyed draws, so results are
 //     independent of the tiling.  In the owner frame one sweep invalidates one
 //     row and one column of the halo on each side.
+#include <type_traits>
+
 #include "device_common.hpp"
 #include "internal.hpp"
 
@@ -158,7 +160,7 @@ __device__ __forceinline__ bool one_bit_colour(const Thr &Tall, uint32_t c)
     return all;
 }
 
-template <int MODE>
+template <int MODE, uint32_t PLANES = 1>
 __device__ __forceinline__ void decide_group(uint32_t key0, uint32_t key1, uint32_t g, uint32_t r, uint32_t t,
                                              uint32_t c, const Thr &Tall, const uint32_t (&R0)[4],
                                              const uint32_t (&vert)[4], const uint32_t (&live)[4], uint32_t (&D)[4])
@@ -176,7 +178,7 @@ __device__ __forceinline__ void decide_group(uint32_t key0, uint32_t key1, uint3
         constexpr int NC = DomCtx<MODE == kMetropolis>::NC;
         uint32_t T[NC], cm[NC][4];
         DomCtx<MODE == kMetropolis>::build(r, c, Tall, vert, T, cm);
-        decide128<NC>(key0, key1, g, r, t, c, T, cm, live, D);
+        decide128<NC, PLANES>(key0, key1, g, r, t, c, T, cm, live, D);
     }
 }
 
@@ -412,7 +414,38 @@ __global__ void __launch_bounds__(1024) domino_tiled_kernel(const uint32_t *__re
 // lane) and, through the carry of the group's last site, bit 0 of those two
 // words of the next group (LDS again).  The rows computed in each step, and
 // every value written, are those of domino_tile.
+//
+// One wavefront per SIMD issues an instruction every 4-5 clocks, so a sweep is
+// bound by the length of its instruction stream, not by bandwidth.  Hence:
+//   * the two colours are straight-line code, one loop per order of them;
+//   * with uniform weights a second wavefront per group (HELP) makes the draws
+//     one barrier ahead and hands them over in LDS: 130 of about 330
+//     instructions a sweep leave the wavefront that holds the state;
+//   * bit-serial decisions draw four planes at a time (heat bath), so that
+//     four Philox chains overlap; a Metropolis threshold is mostly settled by
+//     the first plane;
+//   * where there are more tiles than CUs, a tile without a single rotateable
+//     site is frozen for the whole launch: it takes no sweep, and stores only
+//     words that differ from those of the other buffer (a store that changes
+//     nothing would still be written back at the end of the launch).
+// Per sweep on MI355X, before and after (with longer launches, domino_lengthen):
+// order 1001 uniform 0.87 -> 0.63 us, two-periodic 3.49 -> 2.72, random order
+// 1.20 -> 1.13; order 2048 uniform (5000 sweeps in, 162 of 512 tiles moving)
+// 1.11 -> 0.80; order 4000 uniform 2.61 -> 1.60.  Random order between 256 and
+// 500 tiles does not gain (order 1600 1.64 -> 1.72): two tiles that move often
+// share a CU there.
 constexpr uint32_t kRegRows = 64, kRegGroups = 16;
+constexpr uint32_t kCus = 256;   // compute units of the card
+// Planes per draw of a bit-serial decision: heat bath at order 1001 3.09 us per
+// sweep with 1, 2.87 with 2, 2.82 with 4, 3.05 with 8; Metropolis 2.06 with 1,
+// 2.12 with 4.
+template <int MODE>
+constexpr uint32_t kRegPlanes = MODE == kHeatBath ? 4u : 1u;
+// Draw buffers of HELP.  A barrier per colour step (random order): one is read
+// while the next is filled.  One per sweep: the sweep's second colour reads its
+// draws beyond the barrier, so a third.
+template <bool RANDOM>
+constexpr uint32_t kRegSlots = RANDOM ? 2u : 3u;
 
 // Lane l receives lane l+1's value (lane_next) or lane l-1's (lane_prev);
 // the lane past either end of the wavefront receives 0.
@@ -425,12 +458,12 @@ __device__ __forceinline__ uint32_t lane_prev(uint32_t v)
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x138, 0xF, 0xF, true);   // wave_shr:1
 }
 
-template <int MODE, bool RANDOM>
+template <int MODE, bool RANDOM, bool HELP>
 __global__ void __launch_bounds__(1024) domino_reg_kernel(const uint32_t *__restrict__ in, uint32_t *__restrict__ out,
                                                           size_t PS, uint32_t RS, uint32_t ng, uint32_t n,
                                                           uint32_t omega, uint32_t t0, uint32_t nsweeps, uint32_t TR,
-                                                          uint32_t TG, uint32_t HR, uint32_t HG, uint32_t tiles_x,
-                                                          Thr Tall, uint32_t key0, uint32_t key1)
+                                                          uint32_t TG, uint32_t HR, uint32_t HG, uint32_t span,
+                                                          uint32_t by_rows, uint32_t look, Thr Tall, uint32_t key0, uint32_t key1)
 {
     // First words of E and S published for the previous group, and either the
     // carries (bit-serial decisions: a second barrier) or, for one-bit
@@ -441,135 +474,242 @@ __global__ void __launch_bounds__(1024) domino_reg_kernel(const uint32_t *__rest
     constexpr bool kOneBarrier = MODE == kUniform;
     __shared__ uint32_t xE[2][kRegGroups][kRegRows], xS[2][kRegGroups][kRegRows], xC[2][kRegGroups][kRegRows];
     uint32_t xb = 0;   // buffer of the next other-colour step
-    const uint32_t tile = xcd_tile(blockIdx.x, gridDim.x);
-    const uint32_t tile_r = tile / tiles_x, tile_g = tile % tiles_x;
+    const uint32_t tile = xcd_tile(blockIdx.x, gridDim.x), hi = tile / span, lo = tile - hi * span;
+    const uint32_t tile_r = by_rows ? hi : lo, tile_g = by_rows ? lo : hi;
     const uint32_t LR = TR + 2 * HR, LG = TG + 2 * HG;
     const int R0 = (int)(tile_r * TR) - (int)HR, G0 = (int)(tile_g * TG) - (int)HG;
     const uint32_t lr = threadIdx.x & (kRegRows - 1u), lg = threadIdx.x / kRegRows;
-    const int gr = R0 + (int)lr, gg = G0 + (int)lg;
+    const int gr = R0 + (int)lr;
+    extern __shared__ uint4 draws[];   // HELP: [slots][LG][64 rows]
+    __shared__ uint32_t s_live[kRegGroups], s_colour[2];
+    constexpr uint32_t kDeal = RANDOM ? 1u : 2u;   // colour steps between two barriers
+    // The waves of `lg` >= LG hold no state: they draw for the group lg - LG.
+    if (HELP && lg >= LG) {
+        const uint32_t hg = lg - LG, hgg = (uint32_t)(G0 + (int)hg);
+        uint4 *const to = draws + hg * kRegRows + lr;
+        // the draws of colour steps kDeal * m, ..., to slot `slot`
+        const auto deal = [&](uint32_t m, uint32_t slot) {
+#pragma unroll
+            for (uint32_t i = 0; i < kDeal; ++i) {
+                uint32_t c = i, t = t0 + m;
+                if constexpr (RANDOM) {
+                    t = 2u * t0 + m;
+                    c = step_colour(t, 2u, key0, key1);
+                    if (threadIdx.x == LG * kRegRows) s_colour[slot] = c;
+                }
+                uint32_t R[4];
+                philox4x32_10(hgg, (uint32_t)gr, t, c, key0, key1, R);
+                to[(slot * kDeal + i) * LG * kRegRows] = make_uint4(~R[0], ~R[1], ~R[2], ~R[3]);
+            }
+        };
+        deal(0u, 0u);
+        __syncthreads();
+        if (__ballot((threadIdx.x & 63u) < LG && s_live[threadIdx.x & 63u]) == 0ull) return;
+        const uint32_t deals = 2u * nsweeps / kDeal;
+        uint32_t slot = 0;
+        for (uint32_t m = 1; m <= deals; ++m) {
+            slot = slot + 1u == kRegSlots<RANDOM> ? 0u : slot + 1u;
+            if (m < deals) deal(m, slot);
+            __syncthreads();
+        }
+        return;
+    }
+    const int gg = G0 + (int)lg;
     const bool mine = lr < LR && gr >= 0 && gr < (int)n && gg >= 0 && gg < (int)ng;
     uint32_t N[4] = {0u, 0u, 0u, 0u}, S[4] = {0u, 0u, 0u, 0u}, E[4] = {0u, 0u, 0u, 0u}, W[4] = {0u, 0u, 0u, 0u};
+    uint32_t s4 = 0u, e4 = 0u;   // the next group's first S and E words
     if (mine) {
         const uint32_t *p = in + (size_t)gr * RS + 4 * gg;
         ld4(p, N);
         ld4(p + PS, S);
         ld4(p + 2 * PS, E);
         ld4(p + 3 * PS, W);
+        // (the row has a pad group after its last one, the planes a row)
+        s4 = p[PS + 4];
+        e4 = p[2 * PS + 4];
     }
     const bool has_next = lg + 1u < LG;
-    for (uint32_t s = 0; s < nsweeps; ++s) {
-        for (uint32_t i = 0; i < 2; ++i) {
-            uint32_t c = i, t = t0 + s, base = HR ? s : 0u, end = HR ? LR - s : LR;
-            if constexpr (RANDOM) {
-                const uint32_t step = 2u * t + i, q = 2u * s + i;
-                c = step_colour(step, 2u, key0, key1);
-                t = step;
-                base = HR ? q : 0u;
-                end = HR ? LR - q : LR;
-            }
-            const bool act = mine && lr >= base && lr < end;
-            uint32_t R0v[4] = {0u, 0u, 0u, 0u};
-            if (MODE == kUniform) philox4x32_10((uint32_t)gg, (uint32_t)gr, t, c, key0, key1, R0v);
-            if (c == omega) {
-                uint32_t horiz[4], vert[4], live[4], any = 0u;
+    const bool inner = mine && lr >= HR && lr < HR + TR && lg >= HG && lg < HG + TG;
+    // (look: only where tiles queue for CUs, where an early end frees one)
+    uint32_t any0 = look ? 0u : 1u;
+    if (look) {
+        uint32_t S1[4];
 #pragma unroll
-                for (int w = 0; w < 4; ++w) {
-                    horiz[w] = N[w] & S[w];
-                    vert[w] = E[w] & W[w];
-                    live[w] = horiz[w] | vert[w];
-                    any |= live[w];
-                }
-                if (act && any) {
-                    uint32_t D[4];
-                    decide_group<MODE>(key0, key1, (uint32_t)gg, (uint32_t)gr, t, c, Tall, R0v, vert, live, D);
+        for (int w = 0; w < 4; ++w) S1[w] = lane_next(S[w]);
+        const uint32_t sEdge = lane_next(s4);
 #pragma unroll
-                    for (int w = 0; w < 4; ++w) {
-                        const uint32_t F = (horiz[w] & D[w]) | (vert[w] & ~D[w]);
-                        N[w] ^= F;
-                        S[w] ^= F;
-                        E[w] ^= F;
-                        W[w] ^= F;
-                    }
-                }
-            } else {
-                uint32_t S1[4], W1[4];
-#pragma unroll
-                for (int w = 0; w < 4; ++w) {
-                    S1[w] = lane_next(S[w]);
-                    W1[w] = lane_next(W[w]);
-                }
-                xE[xb][lg][lr] = E[0];
-                xS[xb][lg][lr] = S[0];
-                if constexpr (kOneBarrier) {
-                    // the last site (127) of this group: its N bit, the W bit of
-                    // the row above, its decision, and whether it may flip
-                    const uint32_t may = act && lr + 1u < LR ? 8u : 0u;
-                    xC[xb][lg][lr] = (N[3] >> 31) | ((W1[3] >> 31) << 1) | ((~R0v[3] >> 31) << 2) | may;
-                }
-                __syncthreads();
-                const uint32_t eNext = has_next ? xE[xb][lg + 1][lr] : 0u;
-                const uint32_t sNext = has_next && lr + 1u < kRegRows ? xS[xb][lg + 1][lr + 1] : 0u;
-                // carry in from the previous group's last site, which flips with
-                // this group's first E bit of this row and S bit of the row above
-                uint32_t cin = 0u;
-                if constexpr (kOneBarrier) {
-                    if (lg > 0u) {
-                        const uint32_t P = xC[xb][lg - 1][lr];
-                        const uint32_t hz = S1[0] & P, vt = (P >> 1) & E[0], d = P >> 2;
-                        cin = ((hz & d) | (vt & ~d)) & (P >> 3) & 1u;
-                    }
-                }
-                uint32_t horiz[4], vert[4], live[4], any = 0u;
-#pragma unroll
-                for (int w = 0; w < 4; ++w) {
-                    const uint32_t eHi = (w < 3) ? E[w + 1] : eNext;
-                    const uint32_t sHi = (w < 3) ? S1[w + 1] : sNext;
-                    const uint32_t sN = (S1[w] >> 1) | (sHi << 31);
-                    const uint32_t sW = (E[w] >> 1) | (eHi << 31);
-                    horiz[w] = sN & N[w];
-                    vert[w] = W1[w] & sW;
-                    live[w] = horiz[w] | vert[w];
-                    any |= live[w];
-                }
-                uint32_t F[4] = {0u, 0u, 0u, 0u};
-                if (act && lr + 1u < LR && any) {
-                    uint32_t D[4];
-                    decide_group<MODE>(key0, key1, (uint32_t)gg, (uint32_t)gr, t, c, Tall, R0v, vert, live, D);
-#pragma unroll
-                    for (int w = 0; w < 4; ++w) F[w] = (horiz[w] & D[w]) | (vert[w] & ~D[w]);
-                }
-                // own N and E planes (E shifted by one site)
-#pragma unroll
-                for (int w = 0; w < 4; ++w) {
-                    N[w] ^= F[w];
-                    E[w] ^= (F[w] << 1) | (w > 0 ? F[w - 1] >> 31 : 0u);
-                }
-                // the flips of the row above: this row's W and S planes (S shifted)
-                uint32_t Fd[4];
-#pragma unroll
-                for (int w = 0; w < 4; ++w) Fd[w] = lane_prev(F[w]);
-#pragma unroll
-                for (int w = 0; w < 4; ++w) {
-                    W[w] ^= Fd[w];
-                    S[w] ^= (Fd[w] << 1) | (w > 0 ? Fd[w - 1] >> 31 : 0u);
-                }
-                if constexpr (kOneBarrier) {
-                    E[0] ^= cin;
-                    S[0] ^= lane_prev(cin);   // the carry of the row below
-                } else {
-                    xC[0][lg][lr] = F[3] >> 31;
-                    __syncthreads();
-                    if (lg > 0u) {
-                        E[0] ^= xC[0][lg - 1][lr];
-                        if (lr > 0u) S[0] ^= xC[0][lg - 1][lr - 1];
-                    }
-                }
-                xb ^= 1u;
-            }
+        for (int w = 0; w < 4; ++w) {
+            const uint32_t sHi = (w < 3) ? S1[w + 1] : sEdge, eHi = (w < 3) ? E[w + 1] : e4;
+            any0 |= (N[w] & S[w]) | (E[w] & W[w]);
+            any0 |= (N[w] & ((S1[w] >> 1) | (sHi << 31))) | (lane_next(W[w]) & ((E[w] >> 1) | (eHi << 31)));
         }
     }
-    if (mine && lr >= HR && lr < HR + TR && lg >= HG && lg < HG + TG) {
+    const bool wave_live = __ballot(any0 != 0u) != 0ull;
+    if (lr == 0u) s_live[lg] = wave_live;
+    __syncthreads();
+    const bool frozen = __ballot(lr < LG && s_live[lr & (kRegGroups - 1u)]) == 0ull;
+    if (frozen) nsweeps = 0u;
+    const bool may_other = mine && lr + 1u < LR;   // the row above is in the tile
+    // One owner step / one step of the other colour: colour c, counter t of
+    // the draws, valid rows [base, end), plane-0 draws R0 (uniform weights).
+    const auto owner_step = [&](uint32_t c, uint32_t t, uint32_t base, uint32_t end, const uint32_t (&R0v)[4])
+                                __attribute__((always_inline)) {
+        const bool act = mine && lr >= base && lr < end;
+        uint32_t horiz[4], vert[4], live[4], any = 0u, D[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            horiz[w] = act ? N[w] & S[w] : 0u;
+            vert[w] = act ? E[w] & W[w] : 0u;
+            live[w] = horiz[w] | vert[w];
+            any |= live[w];
+        }
+        if (MODE == kUniform || any)
+            decide_group<MODE, kRegPlanes<MODE>>(key0, key1, (uint32_t)gg, (uint32_t)gr, t, c, Tall, R0v, vert, live,
+                                                 D);
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const uint32_t F = (horiz[w] & D[w]) | (vert[w] & ~D[w]);
+            N[w] ^= F;
+            S[w] ^= F;
+            E[w] ^= F;
+            W[w] ^= F;
+        }
+    };
+    const auto other_step = [&](uint32_t c, uint32_t t, uint32_t base, uint32_t end, const uint32_t (&R0v)[4])
+                                __attribute__((always_inline)) {
+        const bool act = may_other && lr >= base && lr < end;
+        uint32_t S1[4], W1[4];
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            S1[w] = lane_next(S[w]);
+            W1[w] = lane_next(W[w]);
+        }
+        xE[xb][lg][lr] = E[0];
+        xS[xb][lg][lr] = S[0];
+        if constexpr (kOneBarrier) {
+            // the last site (127) of this group: its N bit, the W bit of
+            // the row above, its decision, and whether it may flip
+            xC[xb][lg][lr] = (N[3] >> 31) | ((W1[3] >> 31) << 1) | ((~R0v[3] >> 31) << 2) | (act ? 8u : 0u);
+        }
+        __syncthreads();
+        const uint32_t eNext = has_next ? xE[xb][lg + 1][lr] : 0u;
+        const uint32_t sNext = has_next && lr + 1u < kRegRows ? xS[xb][lg + 1][lr + 1] : 0u;
+        // carry in from the previous group's last site, which flips with
+        // this group's first E bit of this row and S bit of the row above
+        uint32_t cin = 0u;
+        if constexpr (kOneBarrier) {
+            if (lg > 0u) {
+                const uint32_t P = xC[xb][lg - 1][lr];
+                const uint32_t hz = S1[0] & P, vt = (P >> 1) & E[0], d = P >> 2;
+                cin = ((hz & d) | (vt & ~d)) & (P >> 3) & 1u;
+            }
+        }
+        uint32_t horiz[4], vert[4], live[4], any = 0u, D[4] = {0u, 0u, 0u, 0u}, F[4];
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const uint32_t eHi = (w < 3) ? E[w + 1] : eNext;
+            const uint32_t sHi = (w < 3) ? S1[w + 1] : sNext;
+            const uint32_t sN = (S1[w] >> 1) | (sHi << 31);
+            const uint32_t sW = (E[w] >> 1) | (eHi << 31);
+            horiz[w] = act ? sN & N[w] : 0u;
+            vert[w] = act ? W1[w] & sW : 0u;
+            live[w] = horiz[w] | vert[w];
+            any |= live[w];
+        }
+        if (MODE == kUniform || any)
+            decide_group<MODE, kRegPlanes<MODE>>(key0, key1, (uint32_t)gg, (uint32_t)gr, t, c, Tall, R0v, vert, live,
+                                                 D);
+#pragma unroll
+        for (int w = 0; w < 4; ++w) F[w] = (horiz[w] & D[w]) | (vert[w] & ~D[w]);
+        // own N and E planes (E shifted by one site)
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            N[w] ^= F[w];
+            E[w] ^= (F[w] << 1) | (w > 0 ? F[w - 1] >> 31 : 0u);
+        }
+        // the flips of the row above: this row's W and S planes (S shifted)
+        uint32_t Fd[4];
+#pragma unroll
+        for (int w = 0; w < 4; ++w) Fd[w] = lane_prev(F[w]);
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            W[w] ^= Fd[w];
+            S[w] ^= (Fd[w] << 1) | (w > 0 ? Fd[w - 1] >> 31 : 0u);
+        }
+        if constexpr (kOneBarrier) {
+            E[0] ^= cin;
+            S[0] ^= lane_prev(cin);   // the carry of the row below
+        } else {
+            xC[0][lg][lr] = F[3] >> 31;
+            __syncthreads();
+            if (lg > 0u) {
+                E[0] ^= xC[0][lg - 1][lr];
+                if (lr > 0u) S[0] ^= xC[0][lg - 1][lr - 1];
+            }
+        }
+        xb ^= 1u;
+    };
+    uint32_t slot = 0;
+    if constexpr (RANDOM) {
+#pragma unroll 1
+        for (uint32_t q = 0; q < 2u * nsweeps; ++q) {
+            const uint32_t step = 2u * t0 + q, base = HR ? q : 0u, end = LR - base;
+            uint32_t R0v[4] = {0u, 0u, 0u, 0u}, c;
+            if constexpr (HELP) {
+                const uint4 d = draws[(slot * LG + lg) * kRegRows + lr];
+                R0v[0] = ~d.x, R0v[1] = ~d.y, R0v[2] = ~d.z, R0v[3] = ~d.w;
+                c = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_colour[slot]);
+                slot ^= 1u;
+            } else {
+                c = step_colour(step, 2u, key0, key1);
+                if (MODE == kUniform) philox4x32_10((uint32_t)gg, (uint32_t)gr, step, c, key0, key1, R0v);
+            }
+            if (c == omega) {
+                owner_step(c, step, base, end, R0v);
+                if constexpr (HELP) __syncthreads();   // the next step's draws
+            } else {
+                other_step(c, step, base, end, R0v);
+            }
+        }
+    } else {
+        const auto sweep = [&](uint32_t s, auto first) __attribute__((always_inline)) {
+            constexpr bool kOwnerFirst = decltype(first)::value;
+            const uint32_t t = t0 + s, base = HR ? s : 0u, end = LR - base;
+            uint32_t Ra[4] = {0u, 0u, 0u, 0u}, Rb[4] = {0u, 0u, 0u, 0u};
+            if constexpr (HELP) {
+                const uint4 a = draws[((slot * 2u) * LG + lg) * kRegRows + lr];
+                const uint4 b = draws[((slot * 2u + 1u) * LG + lg) * kRegRows + lr];
+                Ra[0] = ~a.x, Ra[1] = ~a.y, Ra[2] = ~a.z, Ra[3] = ~a.w;
+                Rb[0] = ~b.x, Rb[1] = ~b.y, Rb[2] = ~b.z, Rb[3] = ~b.w;
+                slot = slot + 1u == kRegSlots<RANDOM> ? 0u : slot + 1u;
+            } else if (MODE == kUniform) {
+                philox4x32_10((uint32_t)gg, (uint32_t)gr, t, 0u, key0, key1, Ra);
+                philox4x32_10((uint32_t)gg, (uint32_t)gr, t, 1u, key0, key1, Rb);
+            }
+            if constexpr (kOwnerFirst) {
+                owner_step(0u, t, base, end, Ra);
+                other_step(1u, t, base, end, Rb);
+            } else {
+                other_step(0u, t, base, end, Ra);
+                owner_step(1u, t, base, end, Rb);
+            }
+        };
+        if (omega == 0u)
+            for (uint32_t s = 0; s < nsweeps; ++s) sweep(s, std::true_type{});
+        else
+            for (uint32_t s = 0; s < nsweeps; ++s) sweep(s, std::false_type{});
+    }
+    if (inner) {
         uint32_t *p = out + (size_t)gr * RS + 4 * gg;
+        if (frozen) {
+            uint32_t o[4][4], differ = 0u;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) ld4(p + q * PS, o[q]);
+#pragma unroll
+            for (int w = 0; w < 4; ++w)
+                differ |= (o[0][w] ^ N[w]) | (o[1][w] ^ S[w]) | (o[2][w] ^ E[w]) | (o[3][w] ^ W[w]);
+            if (!differ) return;
+        }
         st4(p, N);
         st4(p + PS, S);
         st4(p + 2 * PS, E);
@@ -899,6 +1039,20 @@ DominoTile domino_auto_tile(int n, bool random_order, bool weighted)
     return t;
 }
 
+void domino_lengthen(const DominoDev &d, uint32_t nsw, DominoTile *t)
+{
+    if (!t->reg || t->TG == 0) return;
+    const uint32_t tiles_x = (d.ng + t->TG - 1u) / t->TG;
+    for (uint32_t TR : {16u, 24u}) {
+        const uint32_t S = (kRegRows - TR) / 2u / (t->order ? 2u : 1u), tiles = ((uint32_t)d.n + TR - 1u) / TR * tiles_x;
+        if (TR < t->TR && (uint32_t)d.n > kRegRows && tiles <= kCus && nsw >= S) {
+            t->TR = TR;
+            t->S = S;
+            return;
+        }
+    }
+}
+
 bool domino_plan(const DominoDev &d, const DominoTile &tile, uint32_t S_max, TilePlan *p)
 {
     const uint32_t n = (uint32_t)d.n;
@@ -951,16 +1105,41 @@ hipError_t domino_tiled_sweeps(DominoDev &d, const DominoTile &tile, uint32_t t0
     while (done < nsw) {
         TilePlan p;
         if (!domino_plan(d, tile, nsw - done, &p)) return hipErrorInvalidConfiguration;
-#define TL_DOMINO_PICK(KERNEL)                                                                        \
-    (p.order ? (T.uniform() ? KERNEL<kUniform, true>                                                  \
-                            : (metropolis ? KERNEL<kMetropolis, true> : KERNEL<kHeatBath, true>))    \
-             : (T.uniform() ? KERNEL<kUniform, false>                                                 \
-                            : (metropolis ? KERNEL<kMetropolis, false> : KERNEL<kHeatBath, false>)))
-        auto k = p.reg ? TL_DOMINO_PICK(domino_reg_kernel) : TL_DOMINO_PICK(domino_tiled_kernel);
-#undef TL_DOMINO_PICK
-        hipError_t e = launch(tm, 2 * p.S, k, dim3(p.tiles()), dim3(p.threads), p.lds, s, (const uint32_t *)d.planes,
-                              d.spare, d.PS, d.RS, d.ng, (uint32_t)d.n, (uint32_t)d.omega, t0 + done, p.S, p.TR,
-                              p.TG, p.HR, p.HG, p.tiles_x, T, key0, key1);
+        hipError_t e;
+        if (p.reg) {
+            auto k = p.order ? (T.uniform() ? domino_reg_kernel<kUniform, true, false>
+                                            : (metropolis ? domino_reg_kernel<kMetropolis, true, false>
+                                                          : domino_reg_kernel<kHeatBath, true, false>))
+                             : (T.uniform() ? domino_reg_kernel<kUniform, false, false>
+                                            : (metropolis ? domino_reg_kernel<kMetropolis, false, false>
+                                                          : domino_reg_kernel<kHeatBath, false, false>));
+            uint32_t threads = p.threads, lds = 0u;
+            if (T.uniform() && threads <= 512u) {
+                k = p.order ? domino_reg_kernel<kUniform, true, true> : domino_reg_kernel<kUniform, false, true>;
+                lds = threads * (p.order ? kRegSlots<true> : 2u * kRegSlots<false>) * 16u;
+                threads *= 2u;
+            }
+            // Tiles go to the XCDs in contiguous ranges (xcd_tile), counted
+            // along the rows, or down the columns of tiles where each XCD gets
+            // whole columns: the tiles that then share a CU are 32 apart down
+            // a column and seldom both in the band that moves (order 1950
+            // uniform 0.95 us per sweep by rows, 0.77 by columns), while parts
+            // of columns share fewer halos (1600: 0.93 by rows, 0.99).
+            const uint32_t by_rows = p.tiles_x % 8u != 0u;
+            e = launch(tm, 2 * p.S, k, dim3(p.tiles()), dim3(threads), lds, s, (const uint32_t *)d.planes, d.spare,
+                       d.PS, d.RS, d.ng, (uint32_t)d.n, (uint32_t)d.omega, t0 + done, p.S, p.TR, p.TG, p.HR, p.HG,
+                       by_rows ? p.tiles_x : p.tiles_y, by_rows, p.tiles() > kCus, T, key0, key1);
+        } else {
+            auto k = p.order ? (T.uniform() ? domino_tiled_kernel<kUniform, true>
+                                            : (metropolis ? domino_tiled_kernel<kMetropolis, true>
+                                                          : domino_tiled_kernel<kHeatBath, true>))
+                             : (T.uniform() ? domino_tiled_kernel<kUniform, false>
+                                            : (metropolis ? domino_tiled_kernel<kMetropolis, false>
+                                                          : domino_tiled_kernel<kHeatBath, false>));
+            e = launch(tm, 2 * p.S, k, dim3(p.tiles()), dim3(p.threads), p.lds, s, (const uint32_t *)d.planes, d.spare,
+                       d.PS, d.RS, d.ng, (uint32_t)d.n, (uint32_t)d.omega, t0 + done, p.S, p.TR, p.TG, p.HR, p.HG,
+                       p.tiles_x, T, key0, key1);
+        }
         if (e != hipSuccess) return e;
         uint32_t *tmp = d.planes;
         d.planes = d.spare;

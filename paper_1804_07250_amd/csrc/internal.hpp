@@ -143,6 +143,13 @@ hipError_t domino_colour_step(const DominoDev &d, int colour, uint32_t t, const 
 hipError_t domino_tiled_sweeps(DominoDev &d, const DominoTile &tile, uint32_t t0, uint32_t n, const Thr &T,
                                int metropolis, uint64_t seed, hipStream_t s, Timing *tm = nullptr);
 DominoTile domino_auto_tile(int n, bool random_order, bool weighted = false);
+// Register tiles of fewer owned rows and more sweeps per launch, for a call of
+// nsw sweeps, while every tile still has a compute unit of its own: the work is
+// the same 64 rows per wavefront and the fixed time of a launch (about 4 us) is
+// spread over more sweeps.  Per sweep at order 1001 on MI355X, uniform: 32 rows
+// and 16 sweeps 0.67 us, 16 and 24 0.63; with twice as many tiles as compute
+// units (order 2048: 16 rows 1.02 us, 32 rows 0.77) it loses.
+void domino_lengthen(const DominoDev &d, uint32_t nsw, DominoTile *t);
 hipError_t domino_export(const DominoDev &d, uint8_t *faces, hipStream_t s);
 hipError_t domino_observe(const DominoDev &d, uint32_t B, uint32_t bins_x, unsigned long long *bins,
                           hipStream_t s);

@@ -157,6 +157,8 @@ public:
         tile.order = order;
         if (opt.kernel == 2) tile.reg = 0;
         if (opt.kernel == 3) tile.reg = 1;
+        if (!tuned_rows && !opt.tile_rows && !opt.tile_groups && !opt.sweeps_per_launch)
+            domino_lengthen(d_, n, &tile);
         return domino_tiled_sweeps(d_, tile, t0, n, T, metro ? 1 : 0, seed, s, &timing);
     }
     hipError_t observe(uint32_t B, uint32_t bins_x, unsigned long long *bins, hipStream_t s) override
