@@ -764,6 +764,17 @@ tl_status tl_sampler_sweep(tl_sampler *s, uint64_t n)
     const bool metro = s->w.rule == TL_METROPOLIS;
     const uint32_t every = s->opt.obs_every;
     uint64_t done = 0;
+    // several samples: a model that can takes them inside its launches (one
+    // alone gains little over a launch of its own)
+    if (every && n <= 0xFFFFFFFFull && (s->t + n) / every - s->t / every > 1) {
+        hipError_t e = hipSuccess;
+        if (s->model->sampled_sweeps((uint32_t)s->t, (uint32_t)n, every, s->B, s->bins_x, s->bin_sum, T, metro, s->seed,
+                                     s->opt, s->stream, &e)) {
+            TL_HIP(e);
+            s->samples += (s->t + n) / every - s->t / every;
+            done = n;
+        }
+    }
     while (done < n) {
         const uint32_t t = (uint32_t)(s->t + done);
         // sweeps until the next sample point (or the end)

@@ -150,6 +150,14 @@ DominoTile domino_auto_tile(int n, bool random_order, bool weighted = false);
 // and 16 sweeps 0.67 us, 16 and 24 0.63; with twice as many tiles as compute
 // units (order 2048: 16 rows 1.02 us, 32 rows 0.77) it loses.
 void domino_lengthen(const DominoDev &d, uint32_t nsw, DominoTile *t);
+// Sweeps t0 .. t0+n-1 with a sample into `bins` (bins_x per row, of B x B faces
+// of the whole diamond's box) after each sweep count that `every` divides, in
+// launches that do both; only where domino_samples_inside: one LDS tile and a
+// thread for every word counted.
+bool domino_samples_inside(const DominoDev &d, const DominoTile &tile);
+hipError_t domino_sampled_sweeps(DominoDev &d, const DominoTile &tile, uint32_t t0, uint32_t n, uint32_t every,
+                                 uint32_t B, uint32_t bins_x, unsigned long long *bins, const Thr &T, int metropolis,
+                                 uint64_t seed, hipStream_t s, Timing *tm = nullptr);
 hipError_t domino_export(const DominoDev &d, uint8_t *faces, hipStream_t s);
 hipError_t domino_observe(const DominoDev &d, uint32_t B, uint32_t bins_x, unsigned long long *bins,
                           hipStream_t s);

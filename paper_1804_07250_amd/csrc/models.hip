@@ -127,20 +127,9 @@ public:
         return load_state(d_.planes, d_.spare, host, keep_ext_ ? &ext_[init_max ? 1 : 0] : nullptr, s);
     }
 
-    hipError_t sweeps(uint32_t t0, uint32_t n, const Thr &T, bool metro, uint64_t seed, const tl_options &opt,
-                      hipStream_t s) override
+    // Tile shape of a call: the automatic one, the measured one or the options'.
+    DominoTile tile_of(const Thr &T, const tl_options &opt) const
     {
-        if (opt.kernel == 1) {   // one launch per colour step
-            for (uint32_t i = 0; i < n; ++i)
-                for (uint32_t j = 0; j < 2; ++j) {
-                    const uint32_t step = 2u * (t0 + i) + j;
-                    const int c = order ? (int)host_step_colour(seed, step, 2u) : (int)j;
-                    hipError_t e = domino_colour_step(d_, c, order ? step : t0 + i, T, metro ? 1 : 0, seed, s,
-                                                      &timing);
-                    if (e != hipSuccess) return e;
-                }
-            return hipSuccess;
-        }
         DominoTile tile = domino_auto_tile(d_.n, order != 0, !T.uniform());
         if (tuned_rows) {
             tile.TR = tuned_rows;
@@ -157,9 +146,37 @@ public:
         tile.order = order;
         if (opt.kernel == 2) tile.reg = 0;
         if (opt.kernel == 3) tile.reg = 1;
+        return tile;
+    }
+
+    hipError_t sweeps(uint32_t t0, uint32_t n, const Thr &T, bool metro, uint64_t seed, const tl_options &opt,
+                      hipStream_t s) override
+    {
+        if (opt.kernel == 1) {   // one launch per colour step
+            for (uint32_t i = 0; i < n; ++i)
+                for (uint32_t j = 0; j < 2; ++j) {
+                    const uint32_t step = 2u * (t0 + i) + j;
+                    const int c = order ? (int)host_step_colour(seed, step, 2u) : (int)j;
+                    hipError_t e = domino_colour_step(d_, c, order ? step : t0 + i, T, metro ? 1 : 0, seed, s,
+                                                      &timing);
+                    if (e != hipSuccess) return e;
+                }
+            return hipSuccess;
+        }
+        DominoTile tile = tile_of(T, opt);
         if (!tuned_rows && !opt.tile_rows && !opt.tile_groups && !opt.sweeps_per_launch)
             domino_lengthen(d_, n, &tile);
         return domino_tiled_sweeps(d_, tile, t0, n, T, metro ? 1 : 0, seed, s, &timing);
+    }
+    bool sampled_sweeps(uint32_t t0, uint32_t n, uint32_t every, uint32_t B, uint32_t bins_x, unsigned long long *bins,
+                        const Thr &T, bool metro, uint64_t seed, const tl_options &opt, hipStream_t s,
+                        hipError_t *e) override
+    {
+        if (region_ || opt.kernel == 1) return false;
+        const DominoTile tile = tile_of(T, opt);
+        if (!domino_samples_inside(d_, tile)) return false;
+        *e = domino_sampled_sweeps(d_, tile, t0, n, every, B, bins_x, bins, T, metro ? 1 : 0, seed, s, &timing);
+        return true;
     }
     hipError_t observe(uint32_t B, uint32_t bins_x, unsigned long long *bins, hipStream_t s) override
     {

@@ -26,6 +26,14 @@ public:
     // Sweeps t0 .. t0+n-1, every colour in order 0..K-1 within a sweep.
     virtual hipError_t sweeps(uint32_t t0, uint32_t n, const Thr &T, bool metropolis, uint64_t seed,
                               const tl_options &opt, hipStream_t s) = 0;
+    // Sweeps t0 .. t0+n-1 that also add the observable to the bins, as observe
+    // does, after each sweep count that `every` divides.  False, with nothing
+    // done, if this model or this kind of launch takes its samples apart.
+    virtual bool sampled_sweeps(uint32_t, uint32_t, uint32_t, uint32_t, uint32_t, unsigned long long *, const Thr &,
+                                bool, uint64_t, const tl_options &, hipStream_t, hipError_t *)
+    {
+        return false;
+    }
     // Add the per-cell observable of the current state to bins of B x B cells.
     virtual hipError_t observe(uint32_t B, uint32_t bins_x, unsigned long long *bins, hipStream_t s) = 0;
     virtual void cell_box(uint32_t *w, uint32_t *h) const = 0;
