@@ -183,6 +183,9 @@ struct BatchChain {
 // together.  A bundle of several chains has at most as many (row, group)
 // tasks as the work-group has threads; a single chain may have more.
 constexpr uint32_t kBundleMax = 16;
+// (row, group) tasks of the largest chain that fits in LDS: order 512, 4 groups
+// a row (order 513 has 5 groups and 160 KB of state)
+constexpr uint32_t kBatchTasks = 2048;
 struct BatchBundle {
     uint32_t first, count, tasks, pad;
 };
