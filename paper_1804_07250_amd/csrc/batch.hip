@@ -166,18 +166,22 @@ tl::Model *mask_model(tl_batch *b, int32_t i)
 
 tl_status init_all(tl_batch *b)
 {
+    uint32_t max_words = 0;
     for (int32_t i = 0; i < b->count; ++i) {
+        tl::BatchChain &c = b->chains[i];
         const bool init_max = b->doms[i].init == TL_INIT_MAX;
+        c.t = 0;
+        c.start = init_max ? tl::kStartMax : tl::kStartMin;
         if (tl::Model *m = mask_model(b, i)) {
             TL_HIP(m->init(init_max, b->stream));
+            c.start = tl::kStartHost;
             continue;
         }
-        const tl::DominoDev d = chain_dev(b, i);
-        TL_HIP(tl::domino_init(d, init_max ? 1 : 0, b->stream));
+        max_words = std::max(max_words, c.RS * (c.n + 1u));
     }
-    for (auto &c : b->chains) c.t = 0;
     TL_HIP(hipMemcpyAsync(b->d_chains, b->chains.data(), b->chains.size() * sizeof(tl::BatchChain),
                           hipMemcpyHostToDevice, b->stream));
+    TL_HIP(tl::domino_batch_init(b->d_chains, (uint32_t)b->count, max_words, b->planes, b->stream));
     b->t = 0;
     return TL_OK;
 }
@@ -263,7 +267,7 @@ tl_status tl_batch_create(int32_t n, const tl_domain *doms, const tl_weights *w,
         c.key1 = (uint32_t)(seeds[i] >> 32);
         c.t = 0;
         c.lds_bytes = 4u * c.n * 4u * ng * 4u;
-        c.pad = 0;
+        c.start = tl::kStartMin;   // init_all
         words += (wds + 63) / 64 * 64;   // 256-byte aligned chains
         b->lds_max = std::max(b->lds_max, c.lds_bytes);
         b->sites += b->masks[i] ? b->masks[i]->sites() : 2ull * c.n * c.n - 2ull * c.n + 1ull;

@@ -55,14 +55,10 @@ __device__ __forceinline__ uint32_t brick_pair(int n, int x, int y)
     return (m > 0 && x - 1 >= -m && x <= m - 1 && ((x - 1 + m) & 1) == 0) ? 1u : 0u;
 }
 
-// Writes the initial state into both buffers (a and, if non-null, b),
-// including the zero padding.
-__global__ void domino_init_kernel(uint32_t *a, uint32_t *b, size_t PS, uint32_t RS, int n, int init_max)
+// Word w of row r of the initial state's four planes (zero in the padding).
+__device__ __forceinline__ void init_word(int n, uint32_t r, uint32_t w, int init_max, uint32_t (&bits)[4])
 {
-    const uint32_t w = blockIdx.x * blockDim.x + threadIdx.x;
-    const uint32_t r = blockIdx.y;
-    if (w >= RS || r > (uint32_t)n) return;
-    uint32_t bits[4] = {0u, 0u, 0u, 0u};
+    bits[0] = bits[1] = bits[2] = bits[3] = 0u;
     if (r < (uint32_t)n) {
         for (int bb = 0; bb < 32; ++bb) {
             const int k = (int)(w * 32u) + bb;
@@ -77,11 +73,36 @@ __global__ void domino_init_kernel(uint32_t *a, uint32_t *b, size_t PS, uint32_t
             }
         }
     }
+}
+
+// Writes the initial state into both buffers (a and, if non-null, b),
+// including the zero padding.
+__global__ void domino_init_kernel(uint32_t *a, uint32_t *b, size_t PS, uint32_t RS, int n, int init_max)
+{
+    const uint32_t w = blockIdx.x * blockDim.x + threadIdx.x;
+    const uint32_t r = blockIdx.y;
+    if (w >= RS || r > (uint32_t)n) return;
+    uint32_t bits[4];
+    init_word(n, r, w, init_max, bits);
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
         a[p * PS + (size_t)r * RS + w] = bits[p];
         if (b) b[p * PS + (size_t)r * RS + w] = bits[p];
     }
+}
+
+// The same for every chain of a batch in one launch (chain blockIdx.y): 512
+// launches of 8 us each took 4 ms of a reset.
+__global__ void __launch_bounds__(256) domino_batch_init_kernel(const BatchChain *chains, uint32_t *planes)
+{
+    const BatchChain ch = chains[blockIdx.y];
+    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x, r = i / ch.RS, w = i % ch.RS;
+    if (ch.start == (uint32_t)kStartHost || r > ch.n) return;
+    uint32_t bits[4];
+    init_word((int)ch.n, r, w, ch.start == (uint32_t)kStartMax, bits);
+    uint32_t *a = planes + ch.offset;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) a[p * ch.PS + (size_t)r * ch.RS + w] = bits[p];
 }
 
 __device__ __forceinline__ void ld4(const uint32_t *p, uint32_t (&v)[4])
@@ -1347,6 +1368,20 @@ hipError_t domino_items(const TileJob *jobs, const TileItem *items, uint32_t n_i
     else
         hipLaunchKernelGGL(domino_items_kernel<false>, dim3(n_items), dim3(threads), lds, s, jobs, items);
     return hipGetLastError();
+}
+
+hipError_t domino_batch_init(const BatchChain *chains, uint32_t count, uint32_t max_words, uint32_t *planes,
+                             hipStream_t s)
+{
+    // (the grid's second dimension holds 65535 chains at most)
+    for (uint32_t first = 0; max_words && first < count; first += 65535u) {
+        const uint32_t some = count - first < 65535u ? count - first : 65535u;
+        hipLaunchKernelGGL(domino_batch_init_kernel, dim3((max_words + 255u) / 256u, some), dim3(256), 0, s,
+                           chains + first, planes);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t domino_batch_sweeps(BatchChain *chains, const BatchBundle *bundles, const uint32_t *members,

@@ -177,8 +177,9 @@ struct BatchChain {
     uint32_t key0, key1;
     uint32_t t;        // sweeps done, advanced by the kernel
     uint32_t lds_bytes;
-    uint32_t pad;
+    uint32_t start;    // kStartMin or kStartMax; kStartHost: set up by the host
 };
+enum { kStartMin = 0, kStartMax = 1, kStartHost = 2 };
 // A bundle: chains members[first .. first+count) that one work-group advances
 // together.  A bundle of several chains has at most as many (row, group)
 // tasks as the work-group has threads; a single chain may have more.
@@ -189,6 +190,10 @@ constexpr uint32_t kBatchTasks = 2048;
 struct BatchBundle {
     uint32_t first, count, tasks, pad;
 };
+// The initial state of every chain that is not set up by the host; max_words:
+// the words of the largest one's plane, RS * (n + 1).
+hipError_t domino_batch_init(const BatchChain *chains, uint32_t count, uint32_t max_words, uint32_t *planes,
+                             hipStream_t s);
 // Advance every chain of bundles[0..nbundles) by nsweeps sweeps: one
 // persistent launch; work-groups take bundles from an atomic counter (reset by
 // a small kernel first, so the pair can be captured in a graph).
