@@ -606,11 +606,13 @@ def main():
     achieved = r["bytes_per_launch"] / avg_s / 1e9 if r["launches"] else 0.0
     rec = r["rec"]
     roof = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-            "frac": round(achieved / HBM_PEAK_GBS, 4),
+            "frac": round(achieved / HBM_PEAK_GBS, 4) if achieved <= HBM_PEAK_GBS else None,
             "traffic": rec["bytes_per_launch"] if rec else None,
             "kernel": r["kernel"], "avg_launch_us": round(avg_s * 1e6, 3), "launches": r["launches"],
             "algorithmic_bytes_per_launch": r["bytes_per_launch"],
             "lds": lds_roofline(rec, avg_s), "valu": valu_summary(rec, avg_s), "alu": alu_roofline(rec, avg_s)}
+    if roof["frac"] is None:   # a launch of several sweeps moves the state once, not once per colour step
+        roof["note"] = "streaming-formulation bytes; the tiles stay on chip for a launch, so the HBM figure is not a bound"
     out = {"metric": "site-updates/sec on 1 MI355X (plain vs batched vs served p50/p99), bit-exact",
            "value": r["value"], "unit": "site-updates/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
            "ms_per_step": r["ms_per_step"], "higher_is_better": True, "scaling": "weak",

@@ -547,9 +547,11 @@ __global__ void __launch_bounds__(1024) domino_sample_kernel(const uint32_t *__r
 // share a CU there.
 constexpr uint32_t kRegRows = 64, kRegGroups = 16;
 constexpr uint32_t kCus = 256;   // compute units of the card
-// Planes per draw of a bit-serial decision: heat bath at order 1001 3.09 us per
-// sweep with 1, 2.87 with 2, 2.82 with 4, 3.05 with 8; Metropolis 2.06 with 1,
-// 2.12 with 4.
+// Planes per draw of a bit-serial decision, us per sweep at orders 150 / 1001 /
+// 2048: heat bath 2.92 / 2.87 / 3.09 with 2, 2.83 / 2.98 / 3.02 with 4, 2.89 /
+// 3.05 / 3.28 with 8 (order 1001 3.21 with 1); Metropolis 1.96 / 2.13 / 2.23
+// with 1, 1.95 / 2.12 / 2.20 with 4, 2.86 / 3.06 / 3.08 with 8: most of its
+// sites are settled by the first.
 template <int MODE>
 constexpr uint32_t kRegPlanes = MODE == kHeatBath ? 4u : 1u;
 // Draw buffers of HELP.  A barrier per colour step (random order): one is read
@@ -864,9 +866,9 @@ __global__ void __launch_bounds__(1024) domino_items_kernel(const TileJob *__res
 // A chain alone in its work-group lists the (row, group) tasks with a movable
 // site before each colour step, and only those are decided, 64 to a wavefront:
 // a wavefront stays in the bit-serial comparison as long as any of its lanes,
-// and in a chain some thousand sweeps old only a band moves.  With four planes
-// drawn at a time where few wavefronts are left to overlap.  512 two-periodic
-// chains of orders 16 .. 512, 5000 sweeps, on MI355X: 71 -> 57 ms.
+// and in a chain some thousand sweeps old only a band moves.  Four planes
+// are drawn at a time, as few wavefronts are left to overlap.  4096 two-periodic
+// chains of orders 16 .. 512, 5000 sweeps, on MI355X: 369 -> 316 ms a launch.
 __global__ void batch_reset_kernel(uint32_t *counter) { *counter = 0u; }
 
 template <int MODE, bool RANDOM>
