@@ -594,18 +594,18 @@ __global__ void __launch_bounds__(256) height_step_kernel(uint32_t *planes, size
 //
 // LDS, in words: a guard row, P planes of the state, P planes of the sites
 // that may move (zero outside the tile's inner rows and groups), the stamps of
-// the granules.  Local row lr is global row R0 + lr, local group lg is global group G0 + lg,
-// in slot lg + 1 of its row (the slots around hold the neighbouring groups, or
-// zero).  Rows have an odd number of slots where LDS allows, so that the 16
-// rows of a granule fall in distinct banks; six-vertex rows are kept even rows
-// first, then odd ones, since a colour step takes rows of one parity.
+// the granules, the ring of colours, the tile's flag.  Local row lr is global
+// row R0 + lr, local group lg is global group G0 + lg, in slot lg + 1 of its row
+// (the slots around hold the neighbouring groups, or zero).  Rows have an odd
+// number of slots where LDS allows, so that the 16 rows of a granule fall in
+// distinct banks; six-vertex rows are kept even rows first, then odd ones, since
+// a colour step takes rows of one parity.
 //
 // With a row halo, the rows still valid before sweep s are [rps*s, LR - rps*s)
 // (rps rows go stale per sweep on each side), and only those move.  Under the
 // random colour order (RANDOM) step n of the launch (K per sweep) draws its
 // colour and moves rows [n, LR - n).
 constexpr uint32_t kWindow = 8;       // steps after its last movable site that a granule draws ahead
-constexpr uint32_t kColourRing = 128; // random order: colours of the steps around the current one
 
 // Word at byte offset `at` of a tile's LDS.
 __device__ __forceinline__ uint32_t ldw(const uint32_t *lds, uint32_t at)
@@ -642,8 +642,8 @@ __device__ __forceinline__ void height_tile(uint32_t *lds, const uint32_t *__res
     const uint32_t NG = lay.granules, RB = lay.row_blocks;
     const uint32_t state = LRS, site = state + P * LPS;
     uint32_t *stamp = lds + ((site + P * LPS) >> 2);
-    __shared__ uint32_t s_live;   // the tile has a movable site
-    __shared__ uint32_t s_ring[RANDOM ? kColourRing : 1];
+    uint32_t *const ring = stamp + NG;
+    uint32_t *const live = ring + kColourRing;   // the tile has a movable site
     const int R0 = (int)(tile_r * TR) - (int)HR, G0 = (int)(tile_g * TG) - (int)HG;
     const uint32_t tid = threadIdx.x, nt = blockDim.x, lane = tid & 63u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6), waves = nt >> 6;
@@ -699,12 +699,12 @@ __device__ __forceinline__ void height_tile(uint32_t *lds, const uint32_t *__res
         hst4(lds + (site >> 2) + at, m);
     });
     if constexpr (RANDOM)
-        for (uint32_t i = tid; i < kColourRing; i += nt) s_ring[i] = step_colour(K * t0 + i, K, k0, k1);
+        for (uint32_t i = tid; i < kColourRing; i += nt) ring[i] = step_colour(K * t0 + i, K, k0, k1);
     for (uint32_t i = tid; i < NG; i += nt) stamp[i] = 0u;
-    if (tid == 0u) s_live = 0u;
+    if (tid == 0u) *live = 0u;
     __syncthreads();
 
-    auto colour_of = [&](uint32_t n) { return RANDOM ? s_ring[n & (kColourRing - 1u)] : n % K; };
+    auto colour_of = [&](uint32_t n) { return RANDOM ? ring[n & (kColourRing - 1u)] : n % K; };
     // six-vertex: local rows of a step of colour c are 2i + odd_rows(c)
     auto odd_rows = [&](uint32_t c) { return ((uint32_t)R0 & 1u) ^ (c >> 1); };
 
@@ -872,7 +872,7 @@ __device__ __forceinline__ void height_tile(uint32_t *lds, const uint32_t *__res
             every_colour([&](auto ctag) { any |= look(ctag, l, 0u, LR, [] {}).any; });
             if (any) {
                 stamp[gi] = 1u;
-                s_live = 1u;
+                *live = 1u;
             }
             if (gi == wave) live0 = any != 0u;
         }
@@ -882,7 +882,7 @@ __device__ __forceinline__ void height_tile(uint32_t *lds, const uint32_t *__res
             const uint32_t st = stamp[near];
             return __any(st != 0u && (RANDOM || st + K >= n)) != 0;
         };
-        if (s_live != 0u && NG <= waves) {
+        if (*live != 0u && NG <= waves) {
             // a granule per wavefront, its draws ahead in registers
             uint32_t A[ONEBIT ? 4 : kAheadPlanes], N[ONEBIT ? 4 : kAheadPlanes];
 #pragma unroll
@@ -923,7 +923,7 @@ __device__ __forceinline__ void height_tile(uint32_t *lds, const uint32_t *__res
                     with_colour(c, [&](auto ctag) { step(ctag, n, K * t0 + n, HR ? n : 0u, cn, K * t0 + n + 1u); });
                     c = cn;
                     if (wave == waves - 1u && (n & 63u) == 0u && n)
-                        s_ring[(n + 64u + lane) & (kColourRing - 1u)] = step_colour(K * t0 + n + 64u + lane, K, k0, k1);
+                        ring[(n + 64u + lane) & (kColourRing - 1u)] = step_colour(K * t0 + n + 64u + lane, K, k0, k1);
                     __syncthreads();
                 }
             } else {
@@ -935,7 +935,7 @@ __device__ __forceinline__ void height_tile(uint32_t *lds, const uint32_t *__res
                         __syncthreads();
                     });
             }
-        } else if (s_live != 0u) {
+        } else if (*live != 0u) {
             // more granules than wavefronts: taken in turns, every draw on the spot
             for (uint32_t n = 0; n < steps; ++n) {
                 const uint32_t c = RANDOM ? (uint32_t)__builtin_amdgcn_readfirstlane(colour_of(n)) : n % K;
@@ -952,7 +952,7 @@ __device__ __forceinline__ void height_tile(uint32_t *lds, const uint32_t *__res
                 }
                 if constexpr (RANDOM)
                     if (wave == waves - 1u && (n & 63u) == 0u && n)
-                        s_ring[(n + 64u + lane) & (kColourRing - 1u)] = step_colour(K * t0 + n + 64u + lane, K, k0, k1);
+                        ring[(n + 64u + lane) & (kColourRing - 1u)] = step_colour(K * t0 + n + 64u + lane, K, k0, k1);
                 __syncthreads();
             }
         }

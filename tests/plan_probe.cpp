@@ -1,0 +1,33 @@
+// Launch plans of the library's host code, one request per line of stdin:
+//   height MODEL A B C N ORDER ROWS GROUPS SWEEPS WANTED
+// prints the plan "S TR TG HR HG tiles lds" (LDS bytes), or "refused".
+#include <cstdio>
+#include <cstring>
+
+#include "internal.hpp"
+
+int main()
+{
+    char line[256], what[32];
+    while (std::fgets(line, sizeof line, stdin)) {
+        int at = 0;
+        if (std::sscanf(line, "%31s%n", what, &at) != 1) continue;
+        if (!std::strcmp(what, "height")) {
+            tl::HeightDev d{};
+            tl::HeightTile t;
+            unsigned wanted = 0;
+            if (std::sscanf(line + at, "%d %d %d %d %d %u %u %u %u %u", &d.model, &d.a, &d.b, &d.c, &d.N, &t.order,
+                            &t.TR, &t.TG, &t.S, &wanted) != 10)
+                return 1;
+            (void)tl::height_words(d);
+            tl::TilePlan p;
+            if (tl::height_plan(d, t, wanted, &p))
+                std::printf("%u %u %u %u %u %u %u\n", p.S, p.TR, p.TG, p.HR, p.HG, p.tiles(), p.lds);
+            else
+                std::printf("refused\n");
+        } else {
+            return 1;
+        }
+    }
+    return 0;
+}
