@@ -1421,7 +1421,11 @@ bool height_plan(const HeightDev &d, const HeightTile &tile, uint32_t S_max, Til
     const uint32_t LG0 = TG + (tiles_x > 1 ? 2u : 0u);
     // six-vertex tasks are row pairs (one row of each pair is idle in every
     // colour step), lozenge tasks rows
-    const uint32_t max_rows = (d.model == TL_LOZENGE ? 1u : 2u) * (kTileTasks / LG0);
+    uint32_t max_rows = (d.model == TL_LOZENGE ? 1u : 2u) * (kTileTasks / LG0);
+    // and as many rows as LDS holds: six-vertex rows of one group have 842 of
+    // their 1024.  The shape and the sweeps per launch are upper bounds, clamped
+    // to these rows below.
+    while (max_rows && !height_lds(d.model != TL_LOZENGE, max_rows, LG0).words) --max_rows;
     if (max_rows < 2u * rows_per_sweep + 3u) return false;
     uint32_t TR = tile.TR == 0 ? 1u : (tile.TR < d.rows ? tile.TR : d.rows);
     if (TR < d.rows && TR > max_rows - 2u * rows_per_sweep) TR = max_rows - 2u * rows_per_sweep;
