@@ -141,6 +141,14 @@ tl_status bundle_set(tl_batch *b, uint32_t threads, const tl_batch::BundleSet **
     return TL_OK;
 }
 
+// Does a chain list its movable tasks in work-groups of `threads`?
+bool lists(const tl_batch *b, uint32_t threads)
+{
+    for (const tl::BatchChain &c : b->chains)
+        if (tl::batch_lists(b->T.uniform(), b->metro, c.n * c.ng, threads)) return true;
+    return false;
+}
+
 uint32_t workgroups_for(const tl_batch *b, uint32_t threads, uint32_t bundles)
 {
     // as many resident work-groups per CU as LDS and threads allow
@@ -194,7 +202,7 @@ tl_status launch_direct(tl_batch *b, uint32_t nsweeps, uint32_t threads, tl::Tim
         if (x.threads == threads) st = &x;
     if (!st) return tl::fail(TL_EINVAL, "no bundles for %u threads", threads);
     TL_HIP(tl::domino_batch_sweeps(b->d_chains, st->d_bundles, st->d_members, st->count, b->d_counter, b->planes,
-                                   nsweeps, b->T, b->metro ? 1 : 0, b->colour_order, threads,
+                                   nsweeps, b->T, b->metro ? 1 : 0, b->colour_order, lists(b, threads), threads,
                                    workgroups_for(b, threads, st->count), b->lds_max, b->stream, tm));
     return TL_OK;
 }

@@ -863,15 +863,17 @@ __global__ void __launch_bounds__(1024) domino_items_kernel(const TileJob *__res
 // the members back.  Several small chains share a work-group, so a chain too
 // small to keep a CU busy no longer holds one alone.  Every work-group leaves
 // the loop once the counter passes the end of the list.
-// A chain alone in its work-group lists the (row, group) tasks with a movable
-// site before each colour step, and only those are decided, 64 to a wavefront:
-// a wavefront stays in the bit-serial comparison as long as any of its lanes,
-// and in a chain some thousand sweeps old only a band moves.  Four planes
-// are drawn at a time, as few wavefronts are left to overlap.  4096 two-periodic
-// chains of orders 16 .. 512, 5000 sweeps, on MI355X: 369 -> 316 ms a launch.
+// A large chain alone in its work-group lists the (row, group) tasks with a
+// movable site before each colour step, and only those are decided, 64 to a
+// wavefront (batch_lists): a wavefront stays in the bit-serial comparison as long
+// as any of its lanes, and in a chain some thousand sweeps old only a band moves.
+// Four planes are drawn at a time, as few wavefronts are left to overlap.  4096
+// two-periodic chains of orders 16 .. 512, 5000 sweeps, on MI355X: 369 -> 316 ms a
+// launch.
 __global__ void batch_reset_kernel(uint32_t *counter) { *counter = 0u; }
 
-template <int MODE, bool RANDOM>
+// (LISTS: some chain of the batch lists its tasks.)
+template <int MODE, bool RANDOM, bool LISTS>
 __global__ void __launch_bounds__(1024) domino_batch_kernel(BatchChain *chains, const BatchBundle *bundles,
                                                             const uint32_t *members, uint32_t nbundles,
                                                             uint32_t *counter, uint32_t *planes, uint32_t nsweeps,
@@ -881,7 +883,7 @@ __global__ void __launch_bounds__(1024) domino_batch_kernel(BatchChain *chains, 
     __shared__ uint32_t s_next;
     __shared__ uint32_t s_first[kBundleMax + 1];   // first task of each member (prefix of n * ng)
     __shared__ uint32_t s_off[kBundleMax];         // LDS word offset of each member
-    __shared__ uint16_t s_list[kBatchTasks];       // tasks of a colour step with a movable site
+    __shared__ uint16_t s_list[LISTS ? kBatchTasks : 1u];   // tasks of a colour step with a movable site
     __shared__ uint32_t s_count[2];
     const uint32_t tid = threadIdx.x, nt = blockDim.x;
     for (;;) {
@@ -892,7 +894,7 @@ __global__ void __launch_bounds__(1024) domino_batch_kernel(BatchChain *chains, 
         if (bi >= nbundles) return;
         const BatchBundle B = bundles[bi];
         if (tid == 0) {
-            s_count[0] = 0u;
+            if constexpr (LISTS) s_count[0] = 0u;
             uint32_t task = 0, off = 0;
             for (uint32_t k = 0; k < B.count; ++k) {
                 const BatchChain &ch = chains[members[B.first + k]];
@@ -923,45 +925,70 @@ __global__ void __launch_bounds__(1024) domino_batch_kernel(BatchChain *chains, 
             const BatchChain ch = chains[members[B.first]];
             const uint32_t n = ch.n, ng = ch.ng, LRS = 4 * ng, LPS = n * LRS, omega = (n + 1) & 1u;
             const uint32_t tasks = n * ng;
-            uint32_t turn = 0;   // counter of the list in use
-            for (uint32_t s = 0; s < nsweeps; ++s) {
-                for (uint32_t i = 0; i < 2; ++i) {
-                    uint32_t c = i, t = ch.t + s;
-                    if constexpr (RANDOM) {
-                        t = 2u * t + i;
-                        c = step_colour(t, 2u, ch.key0, ch.key1);
+            if (!LISTS || !batch_lists(MODE == kUniform, MODE == kMetropolis, tasks, nt)) {
+                for (uint32_t s = 0; s < nsweeps; ++s) {
+                    for (uint32_t i = 0; i < 2; ++i) {
+                        uint32_t c = i, t = ch.t + s;
+                        if constexpr (RANDOM) {
+                            t = 2u * t + i;
+                            c = step_colour(t, 2u, ch.key0, ch.key1);
+                        }
+                        for (uint32_t task = tid; task < tasks; task += nt) {
+                            const uint32_t r = task / ng, gg = task % ng;
+                            uint32_t *pN = lds + r * LRS + 4 * gg;
+                            if (c == omega)
+                                owner_group<MODE>(pN, pN + LPS, pN + 2 * LPS, pN + 3 * LPS, r, gg, c, t, Tall, ch.key0,
+                                                  ch.key1);
+                            else if (r + 1 < n)
+                                other_group<MODE>(pN, pN + 2 * LPS, pN + LPS + LRS, pN + 3 * LPS + LRS, r, gg, c, t,
+                                                  Tall, ch.key0, ch.key1, gg + 1 < ng);
+                        }
+                        __syncthreads();
                     }
-                    // the tasks with a movable site, then those alone, 64 a wave
-                    for (uint32_t first = 0; first < tasks; first += nt) {
-                        const uint32_t task = first + tid, r = task / ng, gg = task - r * ng;
-                        const uint32_t *pN = lds + r * LRS + 4 * gg;
-                        bool live = false;
-                        if (task < tasks && c == omega)
-                            live = owner_movable(pN, pN + LPS, pN + 2 * LPS, pN + 3 * LPS);
-                        else if (task < tasks && r + 1 < n)
-                            live = other_movable(pN, pN + 2 * LPS, pN + LPS + LRS, pN + 3 * LPS + LRS, gg + 1 < ng);
-                        const unsigned long long m = __ballot(live);
-                        if (m == 0ull) continue;
-                        uint32_t at = 0;
-                        if ((tid & 63u) == 0u) at = atomicAdd(&s_count[turn], (uint32_t)__popcll(m));
-                        at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
-                        if (live) s_list[at + (uint32_t)__popcll(m & ((1ull << (tid & 63u)) - 1ull))] = (uint16_t)task;
+                }
+            } else if constexpr (LISTS) {
+                uint32_t turn = 0;   // counter of the list in use
+                for (uint32_t s = 0; s < nsweeps; ++s) {
+                    for (uint32_t i = 0; i < 2; ++i) {
+                        uint32_t c = i, t = ch.t + s;
+                        if constexpr (RANDOM) {
+                            t = 2u * t + i;
+                            c = step_colour(t, 2u, ch.key0, ch.key1);
+                        }
+                        // the tasks with a movable site, then those alone, 64 a wave
+                        for (uint32_t first = 0; first < tasks; first += nt) {
+                            const uint32_t task = first + tid, r = task / ng, gg = task - r * ng;
+                            const uint32_t *pN = lds + r * LRS + 4 * gg;
+                            bool live = false;
+                            if (task < tasks && c == omega)
+                                live = owner_movable(pN, pN + LPS, pN + 2 * LPS, pN + 3 * LPS);
+                            else if (task < tasks && r + 1 < n)
+                                live = other_movable(pN, pN + 2 * LPS, pN + LPS + LRS, pN + 3 * LPS + LRS, gg + 1 < ng);
+                            const unsigned long long m = __ballot(live);
+                            if (m == 0ull) continue;
+                            uint32_t at = 0;
+                            if ((tid & 63u) == 0u) at = atomicAdd(&s_count[turn], (uint32_t)__popcll(m));
+                            at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+                            if (live)
+                                s_list[at + (uint32_t)__popcll(m & ((1ull << (tid & 63u)) - 1ull))] = (uint16_t)task;
+                        }
+                        __syncthreads();
+                        const uint32_t count = s_count[turn];
+                        turn ^= 1u;
+                        if (tid == 0) s_count[turn] = 0u;
+                        for (uint32_t q = tid; q < count; q += nt) {
+                            const uint32_t task = s_list[q], r = task / ng, gg = task - r * ng;
+                            uint32_t *pN = lds + r * LRS + 4 * gg;
+                            if (c == omega)
+                                owner_group<MODE, kRegPlanes<MODE>>(pN, pN + LPS, pN + 2 * LPS, pN + 3 * LPS, r, gg, c,
+                                                                    t, Tall, ch.key0, ch.key1);
+                            else
+                                other_group<MODE, kRegPlanes<MODE>>(pN, pN + 2 * LPS, pN + LPS + LRS,
+                                                                    pN + 3 * LPS + LRS, r, gg, c, t, Tall, ch.key0,
+                                                                    ch.key1, gg + 1 < ng);
+                        }
+                        __syncthreads();
                     }
-                    __syncthreads();
-                    const uint32_t count = s_count[turn];
-                    turn ^= 1u;
-                    if (tid == 0) s_count[turn] = 0u;
-                    for (uint32_t q = tid; q < count; q += nt) {
-                        const uint32_t task = s_list[q], r = task / ng, gg = task - r * ng;
-                        uint32_t *pN = lds + r * LRS + 4 * gg;
-                        if (c == omega)
-                            owner_group<MODE, kRegPlanes<MODE>>(pN, pN + LPS, pN + 2 * LPS, pN + 3 * LPS, r, gg, c, t,
-                                                                Tall, ch.key0, ch.key1);
-                        else
-                            other_group<MODE, kRegPlanes<MODE>>(pN, pN + 2 * LPS, pN + LPS + LRS, pN + 3 * LPS + LRS,
-                                                                r, gg, c, t, Tall, ch.key0, ch.key1, gg + 1 < ng);
-                    }
-                    __syncthreads();
                 }
             }
         } else {
@@ -1388,21 +1415,21 @@ hipError_t domino_batch_init(const BatchChain *chains, uint32_t count, uint32_t 
 
 hipError_t domino_batch_sweeps(BatchChain *chains, const BatchBundle *bundles, const uint32_t *members,
                                uint32_t nbundles, uint32_t *counter, uint32_t *planes, uint32_t nsweeps, const Thr &T,
-                               int metropolis, uint32_t colour_order, uint32_t threads, uint32_t workgroups,
-                               uint32_t lds_bytes, hipStream_t s, Timing *tm)
+                               int metropolis, uint32_t colour_order, bool lists, uint32_t threads,
+                               uint32_t workgroups, uint32_t lds_bytes, hipStream_t s, Timing *tm)
 {
     if (threads == 0 || threads > 1024 || (threads & 63) || lds_bytes > 160u * 1024u - 64u)
         return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL(batch_reset_kernel, dim3(1), dim3(1), 0, s, counter);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    auto k = colour_order
-                 ? (T.uniform() ? domino_batch_kernel<kUniform, true>
-                                : (metropolis ? domino_batch_kernel<kMetropolis, true>
-                                              : domino_batch_kernel<kHeatBath, true>))
-                 : (T.uniform() ? domino_batch_kernel<kUniform, false>
-                                : (metropolis ? domino_batch_kernel<kMetropolis, false>
-                                              : domino_batch_kernel<kHeatBath, false>));
+#define TL_BATCH_PICK(R)                                                                              \
+    (T.uniform()  ? domino_batch_kernel<kUniform, R, false>                                           \
+     : metropolis ? (lists ? domino_batch_kernel<kMetropolis, R, true> : domino_batch_kernel<kMetropolis, R, false>) \
+     : lists      ? domino_batch_kernel<kHeatBath, R, true>                                           \
+                  : domino_batch_kernel<kHeatBath, R, false>)
+    auto k = colour_order ? TL_BATCH_PICK(true) : TL_BATCH_PICK(false);
+#undef TL_BATCH_PICK
     return launch(tm, 2 * nsweeps, k, dim3(workgroups), dim3(threads), lds_bytes, s, chains, bundles, members,
                   nbundles, counter, planes, nsweeps, T);
 }

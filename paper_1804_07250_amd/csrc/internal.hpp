@@ -190,6 +190,25 @@ constexpr uint32_t kBatchTasks = 2048;
 struct BatchBundle {
     uint32_t first, count, tasks, pad;
 };
+// Does a chain alone in a work-group list its tasks with a movable site before
+// each colour step and decide only those?  The list costs a second look at the
+// state and a barrier, and pays where it leaves wavefronts of a bit-serial
+// comparison out: where the tasks take several passes, or heat bath more than 8
+// wavefronts.  Two nearly full passes of a wavefront per SIMD stay two.  us per
+// sweep on MI355X, every task -> the listed ones: 256 two-periodic chains of
+// order 512 (2048 tasks) 18.9 -> 13.3 with 256 threads, 9.97 -> 7.20 with 1024;
+// 300 of order 200 (400 tasks, 256 threads) 7.10 -> 5.67; 300 of order 300 (900
+// tasks, 1024 threads) heat bath 10.5 -> 9.4, Metropolis 8.07 -> 8.07; but 100 of
+// order 256 (512 tasks, 256 threads) 6.39 -> 7.25, 300 of order 257 (771 tasks,
+// 1024 threads) Metropolis 7.06 -> 7.71, 1000 of order 100 (100 tasks, 512
+// threads) 7.4 -> 8.9.  A one-bit decision is a single draw: 256 uniform chains of
+// order 512 6.7 -> 9.3 with 256 threads, 3.8 -> 4.8 with 1024.
+inline __host__ __device__ bool batch_lists(bool one_bit, bool metropolis, uint32_t tasks, uint32_t threads)
+{
+    if (one_bit) return false;
+    if (tasks <= threads) return !metropolis && tasks > 512u;
+    return threads > 256u || 4u * tasks <= 7u * threads || tasks > 2u * threads;
+}
 // The initial state of every chain that is not set up by the host; max_words:
 // the words of the largest one's plane, RS * (n + 1).
 hipError_t domino_batch_init(const BatchChain *chains, uint32_t count, uint32_t max_words, uint32_t *planes,
@@ -198,10 +217,11 @@ hipError_t domino_batch_init(const BatchChain *chains, uint32_t count, uint32_t 
 // persistent launch; work-groups take bundles from an atomic counter (reset by
 // a small kernel first, so the pair can be captured in a graph).
 // colour_order: 0 fixed, 1 random per step (chain by chain, from its key).
+// lists: some chain lists its tasks (batch_lists).
 hipError_t domino_batch_sweeps(BatchChain *chains, const BatchBundle *bundles, const uint32_t *members,
                                uint32_t nbundles, uint32_t *counter, uint32_t *planes, uint32_t nsweeps, const Thr &T,
-                               int metropolis, uint32_t colour_order, uint32_t threads, uint32_t workgroups,
-                               uint32_t lds_bytes, hipStream_t s, Timing *tm = nullptr);
+                               int metropolis, uint32_t colour_order, bool lists, uint32_t threads,
+                               uint32_t workgroups, uint32_t lds_bytes, hipStream_t s, Timing *tm = nullptr);
 
 // ------------------------------------------------------ height-function models
 // Bit-planes of a 1-bit height residual: plane p, row y, word w at

@@ -1,6 +1,8 @@
 // Launch plans of the library's host code, one request per line of stdin:
 //   height MODEL A B C N ORDER ROWS GROUPS SWEEPS WANTED
 // prints the plan "S TR TG HR HG tiles lds" (LDS bytes), or "refused".
+//   batch ONE_BIT METROPOLIS TASKS THREADS
+// prints 1 if a batched chain of that many tasks lists the movable ones.
 #include <cstdio>
 #include <cstring>
 
@@ -25,6 +27,10 @@ int main()
                 std::printf("%u %u %u %u %u %u %u\n", p.S, p.TR, p.TG, p.HR, p.HG, p.tiles(), p.lds);
             else
                 std::printf("refused\n");
+        } else if (!std::strcmp(what, "batch")) {
+            unsigned one_bit, metro, tasks, threads;
+            if (std::sscanf(line + at, "%u %u %u %u", &one_bit, &metro, &tasks, &threads) != 4) return 1;
+            std::printf("%d\n", tl::batch_lists(one_bit != 0, metro != 0, tasks, threads) ? 1 : 0);
         } else {
             return 1;
         }
