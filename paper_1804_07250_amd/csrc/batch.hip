@@ -152,13 +152,8 @@ bool lists(const tl_batch *b, uint32_t threads)
 uint32_t workgroups_for(const tl_batch *b, uint32_t threads, uint32_t bundles)
 {
     // as many resident work-groups per CU as LDS and threads allow
-    uint32_t per_cu = (160u * 1024u) / (b->lds_max + 64u);
-    const uint32_t by_threads = 2048u / threads;
-    if (per_cu > by_threads) per_cu = by_threads;
-    if (per_cu < 1u) per_cu = 1u;
-    uint32_t wg = b->cus * per_cu;
-    if (wg > bundles) wg = bundles;
-    return wg;
+    const uint32_t wg = b->cus * tl::batch_per_cu(b->lds_max, lists(b, threads), threads);
+    return wg > bundles ? bundles : wg;
 }
 
 // The mask model of chain i, attached to the chain's state in the pool.

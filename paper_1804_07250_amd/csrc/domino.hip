@@ -1418,7 +1418,7 @@ hipError_t domino_batch_sweeps(BatchChain *chains, const BatchBundle *bundles, c
                                int metropolis, uint32_t colour_order, bool lists, uint32_t threads,
                                uint32_t workgroups, uint32_t lds_bytes, hipStream_t s, Timing *tm)
 {
-    if (threads == 0 || threads > 1024 || (threads & 63) || lds_bytes > 160u * 1024u - 64u)
+    if (threads == 0 || threads > 1024 || (threads & 63) || lds_bytes + batch_static_lds(lists) > 160u * 1024u)
         return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL(batch_reset_kernel, dim3(1), dim3(1), 0, s, counter);
     hipError_t e = hipGetLastError();

@@ -209,6 +209,16 @@ inline __host__ __device__ bool batch_lists(bool one_bit, bool metropolis, uint3
     if (tasks <= threads) return !metropolis && tasks > 512u;
     return threads > 256u || 4u * tasks <= 7u * threads || tasks > 2u * threads;
 }
+// Static LDS of the batch kernels: the bundle's tables and two counters, and the
+// task list (uint16) of those that list.
+inline uint32_t batch_static_lds(bool lists) { return 4u * (2u * kBundleMax + 4u) + (lists ? 2u * kBatchTasks : 0u); }
+// Work-groups per CU that their LDS and their threads allow.
+inline uint32_t batch_per_cu(uint32_t state_bytes, bool lists, uint32_t threads)
+{
+    const uint32_t by_lds = 160u * 1024u / (state_bytes + batch_static_lds(lists)), by_threads = 2048u / threads;
+    const uint32_t n = by_lds < by_threads ? by_lds : by_threads;
+    return n ? n : 1u;
+}
 // The initial state of every chain that is not set up by the host; max_words:
 // the words of the largest one's plane, RS * (n + 1).
 hipError_t domino_batch_init(const BatchChain *chains, uint32_t count, uint32_t max_words, uint32_t *planes,

@@ -3,6 +3,9 @@
 // prints the plan "S TR TG HR HG tiles lds" (LDS bytes), or "refused".
 //   batch ONE_BIT METROPOLIS TASKS THREADS
 // prints 1 if a batched chain of that many tasks lists the movable ones.
+//   batch_lds STATE_BYTES LISTS THREADS
+// prints the static LDS of the batch kernels (with lists or without) and the
+// work-groups counted per CU.
 #include <cstdio>
 #include <cstring>
 
@@ -31,6 +34,10 @@ int main()
             unsigned one_bit, metro, tasks, threads;
             if (std::sscanf(line + at, "%u %u %u %u", &one_bit, &metro, &tasks, &threads) != 4) return 1;
             std::printf("%d\n", tl::batch_lists(one_bit != 0, metro != 0, tasks, threads) ? 1 : 0);
+        } else if (!std::strcmp(what, "batch_lds")) {
+            unsigned state, lists, threads;
+            if (std::sscanf(line + at, "%u %u %u", &state, &lists, &threads) != 3) return 1;
+            std::printf("%u %u\n", tl::batch_static_lds(lists != 0), tl::batch_per_cu(state, lists != 0, threads));
         } else {
             return 1;
         }

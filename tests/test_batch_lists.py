@@ -29,3 +29,17 @@ def test_kernels_without_lists_hold_none():
     assert len(ks) == 6 and sum("domino_batch_kernelILi2" in n for n in ks) == 2
     for name, k in ks.items():
         assert k[".group_segment_fixed_size"] <= 256, name
+
+
+def test_resident_work_groups(plans):
+    """The work-groups counted per CU fit it with the kernels' own static LDS, and
+    one more would not."""
+    static = {lists: {k[".group_segment_fixed_size"] for n, k in kr.kernels().items()
+                      if "domino_batch_kernelI" in n and ("ELb1EE" if lists else "ELb0EE") in n} for lists in (0, 1)}
+    cases = [(64 * n * -(-n // 128), lists, threads) for n in range(1, 513) for threads in (64, 256, 512, 1024)
+             for lists in (0, 1)]
+    for (state, lists, threads), got in zip(cases, plans(["batch_lds %d %d %d" % c for c in cases])):
+        s, per_cu = map(int, got.split())
+        assert {s} == static[lists]
+        assert 1 <= per_cu <= 2048 // threads and per_cu * (state + s) <= kr.LDS_BYTES
+        assert per_cu == 2048 // threads or (per_cu + 1) * (state + s) > kr.LDS_BYTES
