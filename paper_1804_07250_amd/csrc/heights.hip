@@ -136,6 +136,7 @@ __global__ void height_init_kernel(uint32_t *pa, uint32_t *pb, size_t PS, uint32
 // Decisions of the 128 sites of a group held by one lane (the streaming
 // kernels): the one-bit draw, or the bit-serial comparison.
 struct GroupDraws {
+    static constexpr bool kPairs = false;   // compare() takes every class
     uint32_t k0, k1, g, r, t, c;
     uint32_t R0[4];   // plane 0 (one-bit decisions)
     __device__ __forceinline__ void one_bit(uint32_t (&D)[4]) const
@@ -157,6 +158,7 @@ struct GroupDraws {
 // `ready`; other planes are drawn four at a time by the four lanes of a row,
 // and handed to their words by a transpose over lanes 16 apart.
 struct WordDraws {
+    static constexpr bool kPairs = true;   // compare() takes the classes but 2^31 (metro_classes)
     uint32_t k0, k1, g, r, t, c, q;
     bool ready;   // the same in every lane
     const uint32_t *A;
@@ -170,15 +172,16 @@ struct WordDraws {
         philox4x32_10(g, r, t, c, k0, k1, R);
         D[0] = ~(q < 2u ? (q == 0u ? R[0] : R[1]) : (q == 2u ? R[2] : R[3]));
     }
+    // rest: the sites in none of the classes, whose threshold is 2^31
     template <int NC, uint32_t kPlanes>
     __device__ __forceinline__ void compare(const uint32_t (&T)[NC], const uint32_t (&cm)[NC][1],
-                                            const uint32_t (&live)[1], uint32_t (&D)[1]) const
+                                            const uint32_t (&live)[1], uint32_t (&D)[1], uint32_t rest = 0u) const
     {
         // with several classes, T is kept from being hoisted out of the step
         // loop: the selectors of every plane and class are more scalars than
         // there are registers
         uint32_t Ts[NC];
-        uint32_t half = 0u;   // sites whose threshold is 2^31: plane 0 decides them
+        uint32_t half = rest;   // sites whose threshold is 2^31: plane 0 decides them
 #pragma unroll
         for (int i = 0; i < NC; ++i) {
             Ts[i] = T[i];
@@ -197,7 +200,7 @@ struct WordDraws {
             uint32_t x = 0u, e = ~0u;
 #pragma unroll
             for (int y = 3; y >= 0; --y) {
-                uint32_t tb = 0u;
+                uint32_t tb = j0 == 0u && y == 0 ? rest : 0u;
                 if constexpr (NC == 1) {
                     tb = (uint32_t)((int32_t)(Ts[0] << (j0 + (uint32_t)y)) >> 31);
                 } else {
@@ -229,6 +232,51 @@ struct WordDraws {
         D[0] = lt;
     }
 };
+
+// Classes of a lazy Metropolis decision from those of the local weights, s: the
+// table has two thresholds a class, current state down and up, and one of the
+// two is 2^31 (floor(2^31 min(1, r)) and 2^32 - floor(2^31 min(1, 1 / r)) for a
+// weight ratio r).  Plane 0 decides its sites, so the comparison takes the other
+// one alone, and half the classes.
+template <int NS, uint32_t kPlanes, int W, class Draws>
+__device__ __forceinline__ void metro_compare(const Draws &dr, const uint32_t *Tall, const uint32_t (&s)[NS][W],
+                                              const uint32_t (&cur)[W], const uint32_t (&live)[W], uint32_t (&D)[W])
+{
+    if constexpr (Draws::kPairs) {
+        uint32_t T[NS], cm[NS][W], rest = ~0u;
+#pragma unroll
+        for (int x = 0; x < NS; ++x) {
+            const bool up = Tall[2 * x] == 0x80000000u;
+            T[x] = up ? Tall[2 * x + 1] : Tall[2 * x];
+            cm[x][0] = s[x][0] & (cur[0] ^ (up ? 0u : ~0u));
+            rest &= ~cm[x][0];
+        }
+        dr.template compare<NS, kPlanes>(T, cm, live, D, rest);
+    } else {
+        uint32_t T[2 * NS], cm[2 * NS][W];
+#pragma unroll
+        for (int x = 0; x < NS; ++x) {
+            T[2 * x] = Tall[2 * x];
+            T[2 * x + 1] = Tall[2 * x + 1];
+#pragma unroll
+            for (int w = 0; w < W; ++w) {
+                cm[2 * x][w] = s[x][w] & ~cur[w];
+                cm[2 * x + 1][w] = s[x][w] & cur[w];
+            }
+        }
+        dr.template compare<2 * NS, kPlanes>(T, cm, live, D);
+    }
+}
+// The same for heat bath: a threshold per class.
+template <int NS, uint32_t kPlanes, int W, class Draws>
+__device__ __forceinline__ void heat_compare(const Draws &dr, const uint32_t *Tall, const uint32_t (&s)[NS][W],
+                                             const uint32_t (&live)[W], uint32_t (&D)[W])
+{
+    uint32_t T[NS];
+#pragma unroll
+    for (int x = 0; x < NS; ++x) T[x] = Tall[x];
+    dr.template compare<NS, kPlanes>(T, s, live, D);
+}
 
 // Contexts: lozenge heat-bath 1, Metropolis 2 (current up); six-vertex
 // heat-bath 9 classes 3*sA + sB, Metropolis 18 (2*class + current up), or,
@@ -267,23 +315,15 @@ __device__ __forceinline__ void sixv_free_decide(const Draws &dr, const Thr &Tal
     if constexpr (MODE == kUniform) {
         dr.one_bit(D);
     } else {
-        constexpr int NC = MODE == kMetropolis ? 8 : 4;
-        uint32_t T[NC], cm[NC][W];
-#pragma unroll
-        for (int i = 0; i < NC; ++i) T[i] = Tall.v[Thr::kFreeBase + i];
+        uint32_t s[4][W];
 #pragma unroll
         for (int w = 0; w < W; ++w)
 #pragma unroll
-            for (int x = 0; x < 4; ++x) {
-                const uint32_t m = ((x & 1) ? hSW[w] : ~hSW[w]) & ((x & 2) ? hSE[w] : ~hSE[w]);
-                if (MODE == kMetropolis) {
-                    cm[2 * x][w] = m & ~cur[w];
-                    cm[2 * x + 1][w] = m & cur[w];
-                } else {
-                    cm[x][w] = m;
-                }
-            }
-        dr.template compare<NC, 1>(T, cm, live, D);
+            for (int x = 0; x < 4; ++x) s[x][w] = ((x & 1) ? hSW[w] : ~hSW[w]) & ((x & 2) ? hSE[w] : ~hSE[w]);
+        if constexpr (MODE == kMetropolis)
+            metro_compare<4, 1>(dr, Tall.v + Thr::kFreeBase, s, cur, live, D);
+        else
+            heat_compare<4, 1>(dr, Tall.v + Thr::kFreeBase, s, live, D);
     }
 }
 
@@ -297,33 +337,23 @@ __device__ __forceinline__ void sixv_decide(const Draws &dr, const Thr &Tall, co
         dr.one_bit(D);
     } else if constexpr (KIND == kKindSum) {
         // thresholds that depend on sA + sB only (a = b): 5 classes s = 0..4
-        // (Metropolis: x current state, down then up)
-        constexpr int NC = MODE == kMetropolis ? 10 : 5;
-        uint32_t T[NC], cm[NC][W];
-#pragma unroll
-        for (int i = 0; i < NC; ++i) T[i] = Tall.v[i];
+        uint32_t s[5][W];
 #pragma unroll
         for (int w = 0; w < W; ++w) {
             const uint32_t A0 = ~hNE[w] & ~hSW[w], A1 = hNE[w] ^ hSW[w], A2 = hNE[w] & hSW[w];
             const uint32_t B0 = ~hNW[w] & ~hSE[w], B1 = hNW[w] ^ hSE[w], B2 = hNW[w] & hSE[w];
-            const uint32_t s[5] = {A0 & B0, (A0 & B1) | (A1 & B0), (A0 & B2) | (A1 & B1) | (A2 & B0),
-                                   (A1 & B2) | (A2 & B1), A2 & B2};
-#pragma unroll
-            for (int x = 0; x < 5; ++x) {
-                if constexpr (MODE == kMetropolis) {
-                    cm[2 * x][w] = s[x] & ~cur[w];
-                    cm[2 * x + 1][w] = s[x] & cur[w];
-                } else {
-                    cm[x][w] = s[x];
-                }
-            }
+            s[0][w] = A0 & B0;
+            s[1][w] = (A0 & B1) | (A1 & B0);
+            s[2][w] = (A0 & B2) | (A1 & B1) | (A2 & B0);
+            s[3][w] = (A1 & B2) | (A2 & B1);
+            s[4][w] = A2 & B2;
         }
-        dr.template compare<NC, 1>(T, cm, live, D);
+        if constexpr (MODE == kMetropolis)
+            metro_compare<5, 1>(dr, Tall.v, s, cur, live, D);
+        else
+            heat_compare<5, 1>(dr, Tall.v, s, live, D);
     } else {
-        constexpr int NC = MODE == kMetropolis ? 18 : 9;
-        uint32_t T[NC], cm[NC][W];
-#pragma unroll
-        for (int i = 0; i < NC; ++i) T[i] = Tall.v[i];
+        uint32_t s[9][W];
 #pragma unroll
         for (int w = 0; w < W; ++w) {
             const uint32_t A[3] = {~hNE[w] & ~hSW[w], hNE[w] ^ hSW[w], hNE[w] & hSW[w]};
@@ -331,17 +361,12 @@ __device__ __forceinline__ void sixv_decide(const Draws &dr, const Thr &Tall, co
 #pragma unroll
             for (int i = 0; i < 3; ++i)
 #pragma unroll
-                for (int j = 0; j < 3; ++j) {
-                    const uint32_t m = A[i] & B[j];
-                    if (MODE == kMetropolis) {
-                        cm[2 * (3 * i + j)][w] = m & ~cur[w];
-                        cm[2 * (3 * i + j) + 1][w] = m & cur[w];
-                    } else {
-                        cm[3 * i + j][w] = m;
-                    }
-                }
+                for (int j = 0; j < 3; ++j) s[3 * i + j][w] = A[i] & B[j];
         }
-        dr.template compare<NC, 1>(T, cm, live, D);
+        if constexpr (MODE == kMetropolis)
+            metro_compare<9, 1>(dr, Tall.v, s, cur, live, D);
+        else
+            heat_compare<9, 1>(dr, Tall.v, s, live, D);
     }
 }
 
@@ -1381,9 +1406,13 @@ HeightTile height_auto_tile(const HeightDev &d, bool uniform, bool random_order)
     HeightTile t;
     // Up to 16 granules, a wavefront each: the whole domain in one tile, no halo
     // and no launch after the first (six-vertex N = 200, one-bit: 0.9 us per
-    // sweep where tiles of 16 rows take 1.5).
+    // sweep where tiles of 16 rows take 1.5).  The bit-serial six-vertex steps are
+    // long enough that wavefronts sharing a SIMD hold each other up: up to 5
+    // granules there (us per sweep, whole / 16 rows x 12 sweeps: N = 128, 5
+    // granules, 4.10 / 4.19 heat bath and 4.19 / 4.25 Metropolis; N = 160, 6, 4.77 /
+    // 4.28 and 4.76 / 4.33; N = 255, 8, 5.95 / 4.42 and 5.84 / 4.43).
     const HeightLds whole = height_lds(d.model != TL_LOZENGE, d.rows, d.ng);
-    if (whole.granules <= 16u && whole.words) {
+    if (whole.granules <= (uniform || d.model == TL_LOZENGE ? 16u : 5u) && whole.words) {
         t.TR = d.rows;
         t.TG = d.ng;
         t.S = 1u << 28;

@@ -1,6 +1,8 @@
 // Launch plans of the library's host code, one request per line of stdin:
 //   height MODEL A B C N ORDER ROWS GROUPS SWEEPS WANTED
 // prints the plan "S TR TG HR HG tiles lds" (LDS bytes), or "refused".
+//   height_auto MODEL A B C N ORDER ONE_BIT
+// prints the automatic shape "TR TG S" and the granules of its tiles.
 //   batch ONE_BIT METROPOLIS TASKS THREADS
 // prints 1 if a batched chain of that many tasks lists the movable ones.
 //   batch_lds STATE_BYTES LISTS THREADS
@@ -30,6 +32,18 @@ int main()
                 std::printf("%u %u %u %u %u %u %u\n", p.S, p.TR, p.TG, p.HR, p.HG, p.tiles(), p.lds);
             else
                 std::printf("refused\n");
+        } else if (!std::strcmp(what, "height_auto")) {
+            tl::HeightDev d{};
+            unsigned order, one_bit;
+            if (std::sscanf(line + at, "%d %d %d %d %d %u %u", &d.model, &d.a, &d.b, &d.c, &d.N, &order, &one_bit) != 7)
+                return 1;
+            (void)tl::height_words(d);
+            tl::HeightTile t = tl::height_auto_tile(d, one_bit != 0, order != 0);
+            t.order = order;
+            tl::TilePlan p;
+            if (!tl::height_plan(d, t, 1u << 20, &p)) return 1;
+            std::printf("%u %u %u %u\n", t.TR, t.TG, t.S,
+                        tl::height_lds(d.model != TL_LOZENGE, p.TR + 2u * p.HR, p.TG + 2u * p.HG).granules);
         } else if (!std::strcmp(what, "batch")) {
             unsigned one_bit, metro, tasks, threads;
             if (std::sscanf(line + at, "%u %u %u %u", &one_bit, &metro, &tasks, &threads) != 4) return 1;
