@@ -619,12 +619,12 @@ __global__ void __launch_bounds__(256) height_step_kernel(uint32_t *planes, size
 //
 // LDS, in words: a guard row, P planes of the state, P planes of the sites
 // that may move (zero outside the tile's inner rows and groups), the stamps of
-// the granules, the ring of colours, the tile's flag.  Local row lr is global
-// row R0 + lr, local group lg is global group G0 + lg, in slot lg + 1 of its row
-// (the slots around hold the neighbouring groups, or zero).  Rows have an odd
-// number of slots where LDS allows, so that the 16 rows of a granule fall in
-// distinct banks; six-vertex rows are kept even rows first, then odd ones, since
-// a colour step takes rows of one parity.
+// the granules.  Local row lr is global row R0 + lr, local group lg is global
+// group G0 + lg, in slot lg + 1 of its row (the slots around hold the
+// neighbouring groups, or zero).  Rows have an odd number of slots where LDS
+// allows, so that the 16 rows of a granule fall in distinct banks; six-vertex
+// rows are kept even rows first, then odd ones, since a colour step takes rows of
+// one parity.
 //
 // With a row halo, the rows still valid before sweep s are [rps*s, LR - rps*s)
 // (rps rows go stale per sweep on each side), and only those move.  Under the
@@ -648,10 +648,15 @@ __device__ __forceinline__ uint32_t clamp_mask(int klo, int khi, int wi)
     return (uint32_t)(0xFFFFFFFFull << a) & ~(uint32_t)(0xFFFFFFFFull << b);
 }
 
+// Words the threads of a tile share besides the planned LDS: whether it has a
+// movable site, and the ring of colours.  Declared once in each kernel: as
+// statics of height_tile a multi-job kernel had them once for each of its bodies.
+template <bool RANDOM>
+constexpr uint32_t kCommonWords = RANDOM ? 1u + kColourRing : 1u;
 // GEOM: the model.
 enum { kGeomLozenge = 1, kGeomSixv = 2 };
 template <int MODE, int KIND, bool RANDOM, bool MASKED, int GEOM>
-__device__ __forceinline__ void height_tile(uint32_t *lds, const uint32_t *__restrict__ in,
+__device__ __forceinline__ void height_tile(uint32_t *lds, uint32_t *common, const uint32_t *__restrict__ in,
                                             uint32_t *__restrict__ out, size_t PS, uint32_t RS, uint32_t ng,
                                             uint32_t rows, const Geo &geo, uint32_t t0, uint32_t nsweeps,
                                             uint32_t TR, uint32_t TG, uint32_t HR, uint32_t HG, uint32_t tile_r,
@@ -667,8 +672,7 @@ __device__ __forceinline__ void height_tile(uint32_t *lds, const uint32_t *__res
     const uint32_t NG = lay.granules, RB = lay.row_blocks;
     const uint32_t state = LRS, site = state + P * LPS;
     uint32_t *stamp = lds + ((site + P * LPS) >> 2);
-    uint32_t *const ring = stamp + NG;
-    uint32_t *const live = ring + kColourRing;   // the tile has a movable site
+    uint32_t *const live = common, *const ring = common + 1;   // the tile has a movable site; its colours
     const int R0 = (int)(tile_r * TR) - (int)HR, G0 = (int)(tile_g * TG) - (int)HG;
     const uint32_t tid = threadIdx.x, nt = blockDim.x, lane = tid & 63u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6), waves = nt >> 6;
@@ -1002,10 +1006,12 @@ __global__ void __launch_bounds__(kTileThreads) height_tiled_kernel(const uint32
                                                             uint32_t k0, uint32_t k1)
 {
     extern __shared__ uint32_t lds[];
+    __shared__ uint32_t common[kCommonWords<RANDOM>];
     // plain work-group order: tiles of a hexagon differ in work, and the
     // round-robin dispatch over the XCDs balances them
-    height_tile<MODE, KIND, RANDOM, MASKED, kGeomSixv>(lds, in, out, PS, RS, ng, rows, geo, t0, nsweeps, TR, TG, HR,
-                                                       HG, blockIdx.x / tiles_x, blockIdx.x % tiles_x, T, k0, k1);
+    height_tile<MODE, KIND, RANDOM, MASKED, kGeomSixv>(lds, common, in, out, PS, RS, ng, rows, geo, t0, nsweeps, TR,
+                                                       TG, HR, HG, blockIdx.x / tiles_x, blockIdx.x % tiles_x, T, k0,
+                                                       k1);
 }
 template <int MODE, int KIND, bool RANDOM, bool MASKED>
 __global__ void __launch_bounds__(kTileThreads) loz_tiled_kernel(const uint32_t *__restrict__ in,
@@ -1015,26 +1021,27 @@ __global__ void __launch_bounds__(kTileThreads) loz_tiled_kernel(const uint32_t 
                                                         uint32_t HG, uint32_t tiles_x, Thr T, uint32_t k0, uint32_t k1)
 {
     extern __shared__ uint32_t lds[];
-    height_tile<MODE, kKindClass, RANDOM, MASKED, kGeomLozenge>(lds, in, out, PS, RS, ng, rows, geo, t0, nsweeps,
-                                                                TR, TG, HR, HG, blockIdx.x / tiles_x,
+    __shared__ uint32_t common[kCommonWords<RANDOM>];
+    height_tile<MODE, kKindClass, RANDOM, MASKED, kGeomLozenge>(lds, common, in, out, PS, RS, ng, rows, geo, t0,
+                                                                nsweeps, TR, TG, HR, HG, blockIdx.x / tiles_x,
                                                                 blockIdx.x % tiles_x, T, k0, k1);
 }
 
 // Multi-job kernel: work-group b runs tile items[b].tile of job items[b].job,
 // with that job's geometry, plan, thresholds and key.
 template <int MODE, int KIND, bool RANDOM, bool MASKED>
-__device__ __forceinline__ void height_item(uint32_t *lds, const TileJob &j, uint32_t tile)
+__device__ __forceinline__ void height_item(uint32_t *lds, uint32_t *common, const TileJob &j, uint32_t tile)
 {
     const Geo geo{j.model, j.a, j.b, j.c, j.N, j.site, j.PS, j.RS, j.freep, j.free_side};
     const uint32_t tile_r = tile / j.tiles_x, tile_g = tile % j.tiles_x;
     if (j.model == TL_LOZENGE)   // lozenge tables are always classes
-        height_tile<MODE, kKindClass, RANDOM, MASKED, kGeomLozenge>(lds, j.in, j.out, j.PS, j.RS, j.ng, j.rows, geo,
-                                                                    j.t0, j.S, j.TR, j.TG, j.HR, j.HG, tile_r, tile_g,
-                                                                    j.T, j.key0, j.key1);
+        height_tile<MODE, kKindClass, RANDOM, MASKED, kGeomLozenge>(lds, common, j.in, j.out, j.PS, j.RS, j.ng,
+                                                                    j.rows, geo, j.t0, j.S, j.TR, j.TG, j.HR, j.HG,
+                                                                    tile_r, tile_g, j.T, j.key0, j.key1);
     else
-        height_tile<MODE, KIND, RANDOM, MASKED, kGeomSixv>(lds, j.in, j.out, j.PS, j.RS, j.ng, j.rows, geo, j.t0, j.S,
-                                                           j.TR, j.TG, j.HR, j.HG, tile_r, tile_g, j.T, j.key0,
-                                                           j.key1);
+        height_tile<MODE, KIND, RANDOM, MASKED, kGeomSixv>(lds, common, j.in, j.out, j.PS, j.RS, j.ng, j.rows, geo,
+                                                           j.t0, j.S, j.TR, j.TG, j.HR, j.HG, tile_r, tile_g, j.T,
+                                                           j.key0, j.key1);
 }
 
 // Every job of a launch has the colour order RANDOM, and site planes iff MASKED.
@@ -1043,16 +1050,17 @@ __global__ void __launch_bounds__(kTileThreads) height_items_kernel(const TileJo
                                                                       const TileItem *__restrict__ items)
 {
     extern __shared__ uint32_t lds[];
+    __shared__ uint32_t common[kCommonWords<RANDOM>];
     const TileItem it = items[blockIdx.x];
     const TileJob &j = jobs[it.job];
     if constexpr (MODE == kHeatBath) {
         // one-bit jobs share the heat-bath launches (the lighter kernel body)
         if (j.mode == kUniform) {
-            height_item<kUniform, kKindClass, RANDOM, MASKED>(lds, j, it.tile);
+            height_item<kUniform, kKindClass, RANDOM, MASKED>(lds, common, j, it.tile);
             return;
         }
     }
-    height_item<MODE, KIND, RANDOM, MASKED>(lds, j, it.tile);
+    height_item<MODE, KIND, RANDOM, MASKED>(lds, common, j, it.tile);
 }
 
 // The same with every rule and table layout in one launch: work-group b takes
@@ -1064,16 +1072,17 @@ __global__ void __launch_bounds__(kTileThreads) height_items_mixed_kernel(const 
                                                                             const TileItem *__restrict__ items)
 {
     extern __shared__ uint32_t lds[];
+    __shared__ uint32_t common[kCommonWords<RANDOM>];
     const TileItem it = items[blockIdx.x];
     const TileJob &j = jobs[it.job];
     if (j.mode == kUniform)
-        height_item<kUniform, kKindClass, RANDOM, MASKED>(lds, j, it.tile);
+        height_item<kUniform, kKindClass, RANDOM, MASKED>(lds, common, j, it.tile);
     else if (j.mode == kMetropolis)
-        j.kind == kKindSum ? height_item<kMetropolis, kKindSum, RANDOM, MASKED>(lds, j, it.tile)
-                           : height_item<kMetropolis, kKindClass, RANDOM, MASKED>(lds, j, it.tile);
+        j.kind == kKindSum ? height_item<kMetropolis, kKindSum, RANDOM, MASKED>(lds, common, j, it.tile)
+                           : height_item<kMetropolis, kKindClass, RANDOM, MASKED>(lds, common, j, it.tile);
     else
-        j.kind == kKindSum ? height_item<kHeatBath, kKindSum, RANDOM, MASKED>(lds, j, it.tile)
-                           : height_item<kHeatBath, kKindClass, RANDOM, MASKED>(lds, j, it.tile);
+        j.kind == kKindSum ? height_item<kHeatBath, kKindSum, RANDOM, MASKED>(lds, common, j, it.tile)
+                           : height_item<kHeatBath, kKindClass, RANDOM, MASKED>(lds, common, j, it.tile);
 }
 
 __device__ __forceinline__ uint32_t hbit(const uint32_t *pl, size_t PS, uint32_t RS, uint32_t p, uint32_t y,
@@ -1451,7 +1460,7 @@ bool height_plan(const HeightDev &d, const HeightTile &tile, uint32_t S_max, Til
     // six-vertex tasks are row pairs (one row of each pair is idle in every
     // colour step), lozenge tasks rows
     uint32_t max_rows = (d.model == TL_LOZENGE ? 1u : 2u) * (kTileTasks / LG0);
-    // and as many rows as LDS holds: six-vertex rows of one group have 842 of
+    // and as many rows as LDS holds: six-vertex rows of one group have 848 of
     // their 1024.  The shape and the sweeps per launch are upper bounds, clamped
     // to these rows below.
     while (max_rows && !height_lds(d.model != TL_LOZENGE, max_rows, LG0).words) --max_rows;
@@ -1556,7 +1565,7 @@ hipError_t height_items(const TileJob *jobs, const TileItem *items, uint32_t n_i
                         uint32_t mode, uint32_t kind, uint32_t order, uint32_t masked, hipStream_t s)
 {
     if (n_items == 0) return hipSuccess;
-    if (threads == 0 || threads > kTileThreads || (threads & 63u) || lds > 160u * 1024u || mode > 2u || kind > 1u)
+    if (threads == 0 || threads > kTileThreads || (threads & 63u) || lds > 4u * kLdsWords || mode > 2u || kind > 1u)
         return hipErrorInvalidConfiguration;
     auto k = TL_HEIGHT_PICK_ORDER_MASK(height_items_kernel, (int)mode, (int)kind, order, masked);
     hipLaunchKernelGGL(k, dim3(n_items), dim3(threads), lds, s, jobs, items);
@@ -1567,7 +1576,8 @@ hipError_t height_items_mixed(const TileJob *jobs, const TileItem *items, uint32
                               uint32_t lds, uint32_t order, uint32_t masked, hipStream_t s)
 {
     if (n_items == 0) return hipSuccess;
-    if (threads == 0 || threads > kTileThreads || (threads & 63u) || lds > 160u * 1024u) return hipErrorInvalidConfiguration;
+    if (threads == 0 || threads > kTileThreads || (threads & 63u) || lds > 4u * kLdsWords)
+        return hipErrorInvalidConfiguration;
     auto k = order ? (masked ? height_items_mixed_kernel<true, true> : height_items_mixed_kernel<true, false>)
                    : (masked ? height_items_mixed_kernel<false, true> : height_items_mixed_kernel<false, false>);
     hipLaunchKernelGGL(k, dim3(n_items), dim3(threads), lds, s, jobs, items);

@@ -263,14 +263,13 @@ struct HeightTile {
 inline __host__ __device__ uint32_t height_task_rows(bool sixv, uint32_t LR) { return sixv ? (LR + 1u) / 2u : LR; }
 // LDS of a height tile (kernel and plan agree on it): words per row and rows
 // per plane, granules (16 task rows x one group), words in all (0: does not
-// fit).  The words shared by a tile's threads (its colours, whether it moves)
-// are counted here too: as static LDS they would be there once per kernel body
-// inlined into a multi-job kernel, 4 KB of them, where no plan sees them.
+// fit).
 struct HeightLds {
     uint32_t row_words, plane_rows, task_rows, row_blocks, granules, words;
 };
-constexpr uint32_t kLdsWords = 160u * 256u;   // 160 KB: the tile kernels have no static LDS
 constexpr uint32_t kColourRing = 128;   // random order: colours of the steps around the current one
+// 160 KB, less the tile kernels' static words (a flag and the ring, rounded up)
+constexpr uint32_t kLdsWords = 160u * 256u - (kColourRing + 4u);
 // Planes a granule with bit-serial decisions draws ahead.
 constexpr uint32_t kAheadPlanes = 8u;
 inline __host__ __device__ HeightLds height_lds(bool sixv, uint32_t LR, uint32_t LG)
@@ -284,7 +283,7 @@ inline __host__ __device__ HeightLds height_lds(bool sixv, uint32_t LR, uint32_t
     // an odd number of 4-word slots per row where that fits
     for (uint32_t slots = (LG + 2u) | 1u;; slots = LG + 2u) {
         l.row_words = 4u * slots;
-        l.words = l.row_words * (1u + 2u * P * l.plane_rows) + l.granules + kColourRing + 1u;
+        l.words = l.row_words * (1u + 2u * P * l.plane_rows) + l.granules;
         if (l.words <= kLdsWords || slots == LG + 2u) break;
     }
     if (l.words > kLdsWords) l.words = 0u;

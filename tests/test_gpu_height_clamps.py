@@ -1,4 +1,4 @@
-"""Six-vertex tiles of one group asked for more rows than LDS holds (841, halo
+"""Six-vertex tiles of one group asked for more rows than LDS holds (848, halo
 included): the sweeps per launch are cut to what fits, bit for bit against the
 oracle."""
 import pytest
