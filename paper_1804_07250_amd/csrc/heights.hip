@@ -914,6 +914,10 @@ __device__ __forceinline__ void height_tile(uint32_t *lds, uint32_t *common, con
         if (*live != 0u && NG <= waves) {
             // a granule per wavefront, its draws ahead in registers
             uint32_t A[ONEBIT ? 4 : kAheadPlanes], N[ONEBIT ? 4 : kAheadPlanes];
+            // One-bit: the plane of step n is A[n % 4] where that is the step's
+            // colour, else A[0], the planes moving down one a step: an index by n
+            // would put A in private memory.
+            constexpr bool kIndexed = ONEBIT && !RANDOM && K == 4u;
 #pragma unroll
             for (uint32_t x = 0; x < sizeof(A) / 4u; ++x) A[x] = N[x] = 0u;
             uint32_t seen = live0 && wave < NG ? kWindow : 0u;   // steps left to draw ahead in
@@ -931,9 +935,7 @@ __device__ __forceinline__ void height_tile(uint32_t *lds, uint32_t *common, con
                     if (ahead) draw(first, n + 1u, cn, tn, N);
                 });
                 if (v.any) {
-                    uint32_t a0 = 0u;
-                    if constexpr (ONEBIT) a0 = (n & 2u) ? ((n & 1u) ? A[3] : A[2]) : ((n & 1u) ? A[1] : A[0]);
-                    move(ctag, first, v, t, ready != 0u, ONEBIT ? &a0 : A);
+                    move(ctag, first, v, t, ready != 0u, kIndexed ? A + decltype(ctag)::value : A);
                     stamp[wave] = n + 1u;
                     seen = kWindow;
                 } else if (seen) {
@@ -943,6 +945,9 @@ __device__ __forceinline__ void height_tile(uint32_t *lds, uint32_t *common, con
                     ready = ahead;
 #pragma unroll
                     for (uint32_t x = 0; x < sizeof(A) / 4u; ++x) A[x] = N[x];
+                } else if constexpr (!kIndexed) {
+#pragma unroll
+                    for (uint32_t x = 0; x + 1u < sizeof(A) / 4u; ++x) A[x] = A[x + 1u];
                 }
             };
             if constexpr (RANDOM) {

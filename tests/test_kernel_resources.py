@@ -23,3 +23,13 @@ def test_height_plans_fit_with_the_kernels_static_lds(plans):
     assert len(tiles) > 30
     for name, k in tiles.items():
         assert k[".group_segment_fixed_size"] + largest <= kr.LDS_BYTES, name
+
+
+def test_kernels_keep_their_state_in_registers():
+    """No kernel of a sweep spills or indexes its registers by a variable: private
+    memory is device memory."""
+    sweeps = {n: k for n, k in kr.kernels().items()
+              if re.search(r"(tiled|reg|batch|items|items_mixed|sample|step)_kernel", n)}
+    assert len(sweeps) > 60
+    for name, k in sweeps.items():
+        assert k[".private_segment_fixed_size"] == 0 and k[".vgpr_spill_count"] == 0, name
