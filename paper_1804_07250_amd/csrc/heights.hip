@@ -1442,6 +1442,12 @@ HeightTile height_auto_tile(const HeightDev &d, bool uniform, bool random_order)
     // 8 x 6 1.68, 32 x 16 1.63; random order 16 x 6 2.94, 8 x 3 3.52, 32 x 8 3.04.
     t.TG = d.ng <= 8 ? d.ng : 4;
     if (d.model == TL_LOZENGE) {
+        // (one-bit, 64 rows with the halo: wider tiles would have 16 granules or
+        // more than wavefronts, taken in turns with every draw on the spot.  us per
+        // sweep, 2 groups / all of them up to 8 or 4 with a halo: (1500, 500, 500), 5
+        // groups, 2.53 / 3.60; 1024, 6 groups, 2.56 / 4.21; (2000, 1000, 1000), 8 groups,
+        // 2.84 / 4.63; (100, 100, 1500), 4 groups, 2.99 / 3.77; 3 groups 2.39 / 2.42)
+        if (uniform && d.ng > 3) t.TG = 2;
         t.TR = uniform ? 16 : 8;
         t.S = uniform ? 8 : 4;
     } else {

@@ -21,3 +21,17 @@ def test_whole_six_vertex_domains(plans, order):
         assert (rows, sweeps) == (16, 6 if order else 12) and granules <= 16, N
     for N in (20, 160, 200, 255):
         assert shape(plans, tl.TL_SIXVERTEX, 0, 0, 0, N, order, 1)[0] == N + 1, N
+
+
+@pytest.mark.parametrize("order", [0, 1])
+@pytest.mark.parametrize("abc", [(100, 100, 100), (300, 200, 157), (400, 400, 400), (600, 600, 600), (100, 100, 1500),
+                                 (1500, 500, 500), (1024, 1024, 1024), (2000, 1000, 1000), (3000, 400, 300)])
+def test_one_bit_lozenge_granules(plans, abc, order):
+    """Every granule of a one-bit lozenge tile has a wavefront (with more granules
+    than the 16, taken in turns, wide hexagons took up to 1.3 times as long), and
+    wide ones leave a SIMD no more than their share."""
+    rows, groups, sweeps, granules = shape(plans, tl.TL_LOZENGE, *abc, 0, order, 1)
+    assert granules <= 16
+    ng = -(-((abc[0] + abc[2] + 3) // 3) // 128)
+    if ng > 3 and rows < abc[1] + abc[2] + 1:
+        assert groups == 2
