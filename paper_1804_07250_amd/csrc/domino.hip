@@ -468,8 +468,11 @@ __global__ void __launch_bounds__(1024) domino_tiled_kernel(const uint32_t *__re
 // kSamplePlanes words, plane j holding bit j of each site's count, so that a
 // sample is one LDS read and a ripple of carries, and no atomic.  The counts go
 // to the bins once, at the end of the launch, which takes at most
-// 2^kSamplePlanes - 1 samples.  Order 64, 1000 sweeps with a sample after each
-// into bins of one face: 18.8 ms -> 1.03 ms.
+// 2^kSamplePlanes - 1 samples; a run of sites in one bin is one sum, and few bins
+// are summed in LDS (one global atomic a face took 0.2 ms a launch into 16 bins).
+// us per sweep of 400, samples in launches of their own / an atomic a face / now:
+// order 64, a sample after each sweep into bins of one face 19.1 / 0.91 / 0.91;
+// order 128, a sample every 100 into bins of 64 faces 0.87 / 1.37 / 0.82.
 constexpr uint32_t kSamplePlanes = 10;
 
 template <int MODE, bool RANDOM>
@@ -500,16 +503,56 @@ __global__ void __launch_bounds__(1024) domino_sample_kernel(const uint32_t *__r
                                       carry = c;
                                   }
                               });
-    if (p >= 2u) return;
-    for (uint32_t b = 0; b < 32u && 32u * w + b < n; ++b) {
-        uint32_t c = 0u;
+    // The counts of a word go to the bins run by run: site 32w + b covers faces
+    // (X0 - 1 - b, Y0 + b) and (X0 - b, Y0 + b), and a run is the sites whose face
+    // stays in one bin.  Few bins are summed in LDS first, where the state was.
+    const uint32_t nbins = bins_x * bins_x;
+    const bool local = nbins <= 4u * n * LRS;
+    __syncthreads();
+    if (local)
+        for (uint32_t i = threadIdx.x; i < nbins; i += blockDim.x) lds[i] = 0u;
+    __syncthreads();
+    if (p < 2u) {
+        const uint32_t end = n - 32u * w < 32u ? n - 32u * w : 32u, Y0 = r + 32u * w + 1u - p;
+        uint32_t any = 0u;
 #pragma unroll
-        for (uint32_t j = 0; j < kSamplePlanes; ++j) c |= ((count[j] >> b) & 1u) << j;
-        if (!c) continue;
-        // the faces (X - 1, Y) and (X, Y) beside the crossed edge
-        const uint32_t k = 32u * w + b, X = r + n - k, Y = r + k + 1u - p;
-        atomicAdd(&bins[Y / B * bins_x + (X - 1u) / B], (unsigned long long)c);
-        atomicAdd(&bins[Y / B * bins_x + X / B], (unsigned long long)c);
+        for (uint32_t j = 0; j < kSamplePlanes; ++j) any |= count[j];
+        for (uint32_t d = 0; d < 2u; ++d) {
+            // bin of the first site's face, and sites left until its column and
+            // its row end
+            const uint32_t X0 = r + n - 32u * w - d;
+            uint32_t bx = X0 / B, by = Y0 / B, xleft = X0 - bx * B + 1u, yleft = B - (Y0 - by * B);
+            for (uint32_t at = 0; at < end;) {
+                uint32_t len = xleft < yleft ? xleft : yleft;
+                len = len < end - at ? len : end - at;
+                const uint32_t run = (len < 32u ? (1u << len) - 1u : ~0u) << at;
+                if (any & run) {
+                    uint32_t c = 0u;
+#pragma unroll
+                    for (uint32_t j = 0; j < kSamplePlanes; ++j) c += (uint32_t)__popc(count[j] & run) << j;
+                    if (local)
+                        atomicAdd(&lds[by * bins_x + bx], c);
+                    else
+                        atomicAdd(&bins[by * bins_x + bx], (unsigned long long)c);
+                }
+                at += len;
+                xleft -= len;
+                yleft -= len;
+                if (xleft == 0u) {
+                    --bx;
+                    xleft = B;
+                }
+                if (yleft == 0u) {
+                    ++by;
+                    yleft = B;
+                }
+            }
+        }
+    }
+    if (local) {
+        __syncthreads();
+        for (uint32_t i = threadIdx.x; i < nbins; i += blockDim.x)
+            if (lds[i]) atomicAdd(&bins[i], (unsigned long long)lds[i]);
     }
 }
 
