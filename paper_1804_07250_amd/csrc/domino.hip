@@ -585,9 +585,8 @@ __global__ void __launch_bounds__(1024) domino_sample_kernel(const uint32_t *__r
 // Per sweep on MI355X, before and after (with longer launches, domino_lengthen):
 // order 1001 uniform 0.87 -> 0.63 us, two-periodic 3.49 -> 2.72, random order
 // 1.20 -> 1.13; order 2048 uniform (5000 sweeps in, 162 of 512 tiles moving)
-// 1.11 -> 0.80; order 4000 uniform 2.61 -> 1.60.  Random order between 256 and
-// 500 tiles does not gain (order 1600 1.64 -> 1.72): two tiles that move often
-// share a CU there.
+// 1.11 -> 0.80; order 4000 uniform 2.61 -> 1.60; random order 1600 1.58 -> 1.30, from
+// sweep 1600 on 1.51.
 constexpr uint32_t kRegRows = 64, kRegGroups = 16;
 constexpr uint32_t kCus = 256;   // compute units of the card
 // Planes per draw of a bit-serial decision, us per sweep at orders 150 / 1001 /
@@ -1264,6 +1263,18 @@ void domino_lengthen(const DominoDev &d, uint32_t nsw, DominoTile *t)
             return;
         }
     }
+}
+
+uint32_t domino_spread(const DominoDev &d, const DominoTile &tile, uint32_t t0, uint32_t nsw, DominoTile *late)
+{
+    if (!tile.reg || !tile.order || tile.TR == 0u || tile.TG != 2u) return nsw;
+    const uint32_t n = (uint32_t)d.n, tiles_x = (d.ng + 1u) / 2u, tiles = (n + tile.TR - 1u) / tile.TR * tiles_x;
+    if (tiles_x % 8u == 0u || tiles <= kCus + kCus / 4u || tiles > 2u * kCus) return nsw;
+    *late = tile;
+    late->TR = 24;
+    late->TG = 3;
+    late->S = 10;
+    return t0 >= n ? 0u : nsw < n - t0 ? nsw : n - t0;
 }
 
 bool domino_plan(const DominoDev &d, const DominoTile &tile, uint32_t S_max, TilePlan *p)

@@ -150,6 +150,16 @@ DominoTile domino_auto_tile(int n, bool random_order, bool weighted = false);
 // and 16 sweeps 0.67 us, 16 and 24 0.63; with twice as many tiles as compute
 // units (order 2048: 16 rows 1.02 us, 32 rows 0.77) it loses.
 void domino_lengthen(const DominoDev &d, uint32_t nsw, DominoTile *t);
+// One-bit register tiles in random order, sweeps t0 .. t0+nsw-1: how many of them
+// keep `tile`, the rest taking `late` (nsw: all).  Where tiles are counted along
+// the rows (columns need a multiple of 8 of them) and exceed the CUs by more than
+// a quarter, those that share a CU both lie in the band that moves once it has
+// spread, after some n sweeps; fewer tiles, wider and lower, do better then.  us
+// per sweep on MI355X, 32 rows x 2 groups and 24 x 3, at sweep 1000 and 3000: order
+// 1540 1.33, 1.51 and 1.68, 1.50; 1600 1.29, 1.52 and 1.70, 1.51; 1790 1.30, 1.54 and
+// 1.70, 1.51 (the change, of 400 sweeps each, between 1600 and 2000).  Order 1450
+// (276 tiles) 1.30 and 1.43, 1800 (by columns) 1.37 and 1.52, at any time.
+uint32_t domino_spread(const DominoDev &d, const DominoTile &tile, uint32_t t0, uint32_t nsw, DominoTile *late);
 // Sweeps t0 .. t0+n-1 with a sample into `bins` (bins_x per row, of B x B faces
 // of the whole diamond's box) after each sweep count that `every` divides, in
 // launches that do both; only where domino_samples_inside: one LDS tile and a

@@ -163,10 +163,16 @@ public:
                 }
             return hipSuccess;
         }
-        DominoTile tile = tile_of(T, opt);
-        if (!tuned_rows && !opt.tile_rows && !opt.tile_groups && !opt.sweeps_per_launch)
+        DominoTile tile = tile_of(T, opt), late;
+        uint32_t early = n;
+        if (!tuned_rows && !opt.tile_rows && !opt.tile_groups && !opt.sweeps_per_launch) {
             domino_lengthen(d_, n, &tile);
-        return domino_tiled_sweeps(d_, tile, t0, n, T, metro ? 1 : 0, seed, s, &timing);
+            if (T.uniform()) early = domino_spread(d_, tile, t0, n, &late);
+        }
+        hipError_t e = domino_tiled_sweeps(d_, tile, t0, early, T, metro ? 1 : 0, seed, s, &timing);
+        if (e == hipSuccess && early < n)
+            e = domino_tiled_sweeps(d_, late, t0 + early, n - early, T, metro ? 1 : 0, seed, s, &timing);
+        return e;
     }
     bool sampled_sweeps(uint32_t t0, uint32_t n, uint32_t every, uint32_t B, uint32_t bins_x, unsigned long long *bins,
                         const Thr &T, bool metro, uint64_t seed, const tl_options &opt, hipStream_t s,

@@ -3,6 +3,9 @@
 // prints the plan "S TR TG HR HG tiles lds" (LDS bytes), or "refused".
 //   height_auto MODEL A B C N ORDER ONE_BIT
 // prints the automatic shape "TR TG S" and the granules of its tiles.
+//   domino_auto N ORDER WEIGHTED T0 SWEEPS
+// prints the automatic shape "TR TG S", and of that many sweeps from sweep T0 on
+// how many take it.
 //   batch ONE_BIT METROPOLIS TASKS THREADS
 // prints 1 if a batched chain of that many tasks lists the movable ones.
 //   batch_lds STATE_BYTES LISTS THREADS
@@ -44,6 +47,17 @@ int main()
             if (!tl::height_plan(d, t, 1u << 20, &p)) return 1;
             std::printf("%u %u %u %u\n", t.TR, t.TG, t.S,
                         tl::height_lds(d.model != TL_LOZENGE, p.TR + 2u * p.HR, p.TG + 2u * p.HG).granules);
+        } else if (!std::strcmp(what, "domino_auto")) {
+            tl::DominoDev d{};
+            unsigned order, weighted, t0, sweeps;
+            if (std::sscanf(line + at, "%d %u %u %u %u", &d.n, &order, &weighted, &t0, &sweeps) != 5) return 1;
+            (void)tl::domino_words(d.n, &d.ng, &d.RS, &d.PS);
+            tl::DominoTile t = tl::domino_auto_tile(d.n, order != 0, weighted != 0), late;
+            t.order = order;
+            const unsigned early = weighted ? sweeps : tl::domino_spread(d, t, t0, sweeps, &late);
+            std::printf("%u %u %u %u", t.TR, t.TG, t.S, early);
+            if (early < sweeps) std::printf(" %u %u %u", late.TR, late.TG, late.S);
+            std::printf("\n");
         } else if (!std::strcmp(what, "batch")) {
             unsigned one_bit, metro, tasks, threads;
             if (std::sscanf(line + at, "%u %u %u %u", &one_bit, &metro, &tasks, &threads) != 4) return 1;
