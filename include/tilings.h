@@ -230,9 +230,9 @@ tl_status tl_sampler_create(const tl_domain *dom, const tl_weights *w, uint64_t 
  * on a copy of the state, which the sampler's state and sweep counter never
  * see; the fastest is kept for the sampler's later sweeps (tile fields of its
  * options still take precedence).  With opt->tune_cache set, a shape
- * recorded there for the same model, shape, sizes, table kind, colour order
- * and device is used without probing, and a newly measured one is appended
- * (one text line per entry).  Synchronous.  Errors: TL_EINVAL, TL_ENOMEM,
+ * recorded there for the same model, shape, sizes, table kind, colour order,
+ * device and generation of the kernels is used without probing, and a newly
+ * measured one is appended (one text line per entry).  Synchronous.  Errors: TL_EINVAL, TL_ENOMEM,
  * TL_EDEVICE. */
 typedef struct {
     uint32_t tile_rows, tile_groups, sweeps_per_launch;   /* 0, 0, 0: the automatic shape won */

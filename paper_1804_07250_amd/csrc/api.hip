@@ -451,8 +451,13 @@ tl_status make_free_table(const tl_domain &d, const tl_weights &w, std::vector<u
 
 namespace {
 
+// Generation of the tile kernels: a shape measured with other ones says little
+// (six-vertex N = 777, one-bit, random order, us per sweep: the shape kept for the
+// kernels without granules 3.37 with them, 4.08 now, the automatic one 2.77).
+constexpr const char *kKernelGeneration = "granules2";
+
 // Cache key of a tile shape: model, shape and sizes, table kind, colour
-// order and device (architecture and CU count).
+// order, device (architecture and CU count) and generation of the kernels.
 std::string tune_key(const tl_sampler *s, bool uniform)
 {
     int dev = 0;
@@ -467,7 +472,7 @@ std::string tune_key(const tl_sampler *s, bool uniform)
                     std::to_string(d.a) + "," + std::to_string(d.b) + "," + std::to_string(d.c) + "," +
                     std::to_string(d.w) + "x" + std::to_string(d.h) + "," + std::to_string(s->model->sites()) +
                     ":f" + std::to_string(d.flags) + ":" + (uniform ? "one-bit" : "weighted") + ":o" +
-                    std::to_string(s->opt.colour_order) + ":" + arch;
+                    std::to_string(s->opt.colour_order) + ":" + arch + ":" + kKernelGeneration;
     return k;
 }
 
