@@ -279,8 +279,8 @@ __device__ __forceinline__ void heat_compare(const Draws &dr, const uint32_t *Ta
 }
 
 // Contexts: lozenge heat-bath 1, Metropolis 2 (current up); six-vertex
-// heat-bath 9 classes 3*sA + sB, Metropolis 18 (2*class + current up), or,
-// when a heat-bath table has 5 entries, classes by sA + sB alone.
+// heat-bath 9 classes 3*sA + sB, Metropolis 18 (2*class + current up), or, when
+// the table has 5 or 10 entries, classes by sA + sB alone.
 template <int MODE, int W, class Draws>
 __device__ __forceinline__ void loz_decide(const Draws &dr, const Thr &Tall, const uint32_t (&cur)[W],
                                            const uint32_t (&live)[W], uint32_t (&D)[W])
@@ -1419,8 +1419,8 @@ HeightTile height_auto_tile(const HeightDev &d, bool uniform, bool random_order)
 {
     HeightTile t;
     // Up to 16 granules, a wavefront each: the whole domain in one tile, no halo
-    // and no launch after the first (six-vertex N = 200, one-bit: 0.9 us per
-    // sweep where tiles of 16 rows take 1.5).  The bit-serial six-vertex steps are
+    // and no launch after the first (six-vertex N = 200, one-bit: 1.06 us per
+    // sweep where tiles of 16 rows take 1.26).  The bit-serial six-vertex steps are
     // long enough that wavefronts sharing a SIMD hold each other up: up to 5
     // granules there (us per sweep, whole / 16 rows x 12 sweeps: N = 128, 5
     // granules, 4.10 / 4.19 heat bath and 4.19 / 4.25 Metropolis; N = 160, 6, 4.77 /

@@ -329,8 +329,9 @@ hipError_t loz_region_observe(const HeightDev &d, const int32_t *anchor, const i
 // ------------------------------------------------------ planned tile launches
 // One launch of a tiled multi-sweep kernel, planned on the host: S sweeps,
 // tiles_x * tiles_y tiles of TR rows x TG groups with HR halo rows and HG halo
-// groups on each side, `threads` per work-group (one (row, group) task per
-// thread and row pass), `lds` bytes of LDS per work-group.
+// groups on each side, `threads` per work-group (LDS domino tiles a thread per
+// (row, group) task, register tiles a wavefront per group, height tiles a
+// wavefront per granule, up to 16), `lds` bytes of planned LDS per work-group.
 struct TilePlan {
     uint32_t S = 0, TR = 0, TG = 0, HR = 0, HG = 0, tiles_x = 0, tiles_y = 0, threads = 0, lds = 0;
     uint32_t order = 0;   // colour order of the launch (the halo covers it)
