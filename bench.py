@@ -612,7 +612,15 @@ def main():
             "algorithmic_bytes_per_launch": r["bytes_per_launch"],
             "lds": lds_roofline(rec, avg_s), "valu": valu_summary(rec, avg_s), "alu": alu_roofline(rec, avg_s)}
     if roof["frac"] is None:   # a launch of several sweeps moves the state once, not once per colour step
-        roof["note"] = "streaming-formulation bytes; the tiles stay on chip for a launch, so the HBM figure is not a bound"
+        note = "streaming-formulation bytes; the tiles stay on chip for a launch, so the HBM figure is not a bound"
+        alu = roof.pop("alu")
+        if alu:   # the VALU lane throughput is the roofline then, as for the other forms
+            hbm = hbm_figure(r["bytes_per_launch"], rec, avg_s)
+            hbm["note"] = note
+            roof.update(alu)
+            roof["hbm"] = hbm
+        else:
+            roof.update({"alu": None, "note": note})
     out = {"metric": "site-updates/sec on 1 MI355X (plain vs batched vs served p50/p99), bit-exact",
            "value": r["value"], "unit": "site-updates/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
            "ms_per_step": r["ms_per_step"], "higher_is_better": True, "scaling": "weak",
